@@ -148,15 +148,20 @@ typedef struct lbm_ctx_s *lbm_ctx;
  * touches the GPU.  LBM_ERR_ARG if cap is too small or cfg is invalid. */
 lbm_status lbm_coefficients(const lbm_config *cfg, double *out, int cap, int *n_written);
 
-/* Bytes of device workspace lbm_init needs for cfg (two lattices for the
- * push scheme, one for AA, plus reduction scratch and the staging area of
- * the host lbm_moments, about 4 MB).  Host only. */
+/* Bytes of device workspace lbm_init takes for cfg: two lattices for the push
+ * scheme, one for AA, plus reduction scratch and the staging area of the host
+ * lbm_moments, about 4 MB.  d2v9 boxes with one weight for all cells and a
+ * lattice below 4 GiB run calls of several steps as passes of several steps
+ * from one lattice into another; for AA the value then holds a second lattice
+ * (which overlaps the staging area).  lbm_init accepts an AA workspace without
+ * it, down to one lattice and the staging area: steps then run one by one, in
+ * place, with the same results.  Host only. */
 lbm_status lbm_workspace_bytes(const lbm_config *cfg, size_t *bytes);
 
 /* Create a context and set the populations to equilibrium with the given
  * density and velocity fields (initial condition f = f_eq(n0, u0)).
- *   workspace: device pointer, >= lbm_workspace_bytes(cfg) bytes, 256-byte
- *              aligned; borrowed until lbm_free.
+ *   workspace: device pointer, >= lbm_workspace_bytes(cfg) bytes (see there),
+ *              256-byte aligned; borrowed until lbm_free.
  *   stream:    hipStream_t the context enqueues on (NULL = null stream).
  *   n0_dev:    device float64 [nz][ny][nx] density I_0;
  *   u0_dev:    device float64 [D][nz][ny][nx] velocity u0.
@@ -166,7 +171,9 @@ lbm_status lbm_init(const lbm_config *cfg, void *workspace, size_t bytes, void *
                     const double *n0_dev, const double *u0_dev, lbm_ctx *out);
 
 /* Advance nsteps lattice BGK steps (lattice BGK equation: stream, moments,
- * equilibrium, relaxation), fused into one kernel per step.  Asynchronous. */
+ * equilibrium, relaxation), fused into one kernel per step, or per 2 to 6 steps
+ * (lbm_workspace_bytes; the same results bit for bit).  An even nsteps leaves
+ * the state in the lattice it was in.  Asynchronous. */
 lbm_status lbm_step(lbm_ctx ctx, int64_t nsteps);
 
 /* Density n = I_0 and velocity u0 of the current populations (moment update

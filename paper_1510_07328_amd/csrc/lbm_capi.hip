@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "lbm_internal.h"
+#include "lbm_multi.h"
 
 namespace lbm {
 hipError_t launch_step(int lattice, int fp64, int scheme, int parity, void *a, void *b, const Box &box, const Model &m,
@@ -54,6 +55,8 @@ struct Layout {
     int64_t cells = 0, plane = 0;  // plane: elements between population planes
     int rows = 0;
     size_t elt = 0, lattice_bytes = 0, part_off = 0, out_off = 0, mask_off = 0, stage_off = 0, total = 0;
+    size_t min_total = 0;  // without the second lattice of an AA box whose calls fuse steps
+    bool multi = false;    // calls of several steps run as passes of several steps
     int stage_rows = 0;  // rows of moments staged per chunk of the host lbm_moments
     int nlat = 0;
     bool porous = false;  // obstacles or a body force: link mask in the workspace, porous kernels
@@ -107,7 +110,12 @@ lbm_status check_config(const lbm_config *cfg, Model *m, Layout *lay) {
     if (srows < 1) srows = 1;
     if (srows > rows) srows = rows;
     lay->stage_rows = (int)srows;
-    lay->total = lay->stage_off + align_up((size_t)srows * row_bytes);
+    const size_t stage = align_up((size_t)srows * row_bytes);
+    lay->min_total = lay->total = lay->stage_off + stage;
+    lay->multi = multi_eligible(cfg->lattice, m->local != 0, cfg->nx, cfg->ny, lay->plane, lay->elt);
+    // AA: the second lattice of the passes, which between calls is free for the staging
+    if (lay->multi && lay->nlat == 1)
+        lay->total = lay->stage_off + (lay->lattice_bytes > stage ? lay->lattice_bytes : stage);
     return LBM_OK;
 }
 
@@ -129,33 +137,67 @@ struct lbm_ctx_s {
     double *part = nullptr, *out = nullptr;
     uint32_t *lm = nullptr;  // link mask (porous runs only)
     double F[3] = {0.0, 0.0, 0.0};
-    int cur = 0;          // push: index of the lattice holding the state
+    int cur = 0;          // index of the lattice holding the state
     int64_t steps = 0;    // steps done
     int block = 256;
     int fp64 = 0;
     double rho_ref = 1.0;
     hipStream_t stream = nullptr;
     hipStream_t cap = nullptr;  // private stream for graph capture
+    bool multi = false;   // calls of several steps run as passes between the two lattices
+    MultiPlan plan{};
     hipGraphExec_t graph[2] = {nullptr, nullptr};  // by starting parity / lattice index
 };
 
 namespace {
 
-int phase(const lbm_ctx_s *c) {
-    // push: which lattice is current; AA: parity of the steps done
-    return c->cfg.scheme == LBM_SCHEME_PUSH ? c->cur : (int)(c->steps & 1);
-}
+// AA: parity of the steps done (0: natural layout)
+int parity(const lbm_ctx_s *c) { return c->cfg.scheme == LBM_SCHEME_AA ? (int)(c->steps & 1) : 0; }
 
 hipError_t one_step(lbm_ctx_s *c, hipStream_t s) {
-    const int ph = phase(c);
-    void *a = c->cfg.scheme == LBM_SCHEME_PUSH ? c->lat[ph] : c->lat[0];
-    void *b = c->cfg.scheme == LBM_SCHEME_PUSH ? c->lat[1 - ph] : nullptr;
-    hipError_t e = launch_step(c->model.lattice, c->fp64, c->cfg.scheme, ph, a, b, c->box, c->model, c->cfg.tau,
-                               c->rho_ref, c->block, c->lm, c->F, s);
+    const bool push = c->cfg.scheme == LBM_SCHEME_PUSH;
+    hipError_t e = launch_step(c->model.lattice, c->fp64, c->cfg.scheme, parity(c), c->lat[c->cur],
+                               push ? c->lat[1 - c->cur] : nullptr, c->box, c->model, c->cfg.tau, c->rho_ref, c->block,
+                               c->lm, c->F, s);
     if (e == hipSuccess) {
-        if (c->cfg.scheme == LBM_SCHEME_PUSH) c->cur = 1 - c->cur;
+        if (push) c->cur = 1 - c->cur;
         c->steps++;
     }
+    return e;
+}
+
+// n steps: passes of several steps where the box takes them, else one by one.
+// Passes start and end in natural layout, so an AA run takes an odd step before
+// and after on its own; after n steps the state is in the lattice that n single
+// steps leave it in (a caller may capture the call and replay it).
+hipError_t enqueue_steps(lbm_ctx_s *c, int64_t n, hipStream_t s) {
+    const bool aa = c->cfg.scheme == LBM_SCHEME_AA;
+    hipError_t e = hipSuccess;
+    if (c->multi) {
+        if (n > 0 && parity(c)) {
+            e = one_step(c, s);
+            --n;
+        }
+        int64_t m = aa ? n & ~int64_t(1) : n;
+        n -= m;
+        for (int odd = aa ? 0 : (int)(m & 1); m > 0 && e == hipSuccess; odd ^= 1) {
+            const int H = multi_depth(c->plan, m, odd);
+            if (H < 2) {
+                if (H == 0) break;
+                e = one_step(c, s);
+            } else {
+                e = launch_multi(c->fp64, H, c->lat[c->cur], c->lat[1 - c->cur], c->lm, c->box, c->model, c->cfg.tau,
+                                 c->rho_ref, c->F, c->plan.ly[H], s);
+                if (e == hipSuccess) {
+                    c->cur = 1 - c->cur;
+                    c->steps += H;
+                }
+            }
+            m -= H;
+        }
+        n += m;
+    }
+    for (; n > 0 && e == hipSuccess; --n) e = one_step(c, s);
     return e;
 }
 
@@ -169,8 +211,7 @@ lbm_status build_graph(lbm_ctx_s *c, int ph) {
     const int64_t save_steps = c->steps;
     e = hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
-    hipError_t le = hipSuccess;
-    for (int k = 0; k < c->cfg.graph_steps && le == hipSuccess; ++k) le = one_step(c, c->cap);
+    const hipError_t le = enqueue_steps(c, c->cfg.graph_steps, c->cap);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(c->cap, &g);
     c->cur = save_cur;
@@ -241,7 +282,7 @@ lbm_status lbm_init(const lbm_config *cfg, void *workspace, size_t bytes, void *
     Layout lay;
     lbm_status s = check_config(cfg, &m, &lay);
     if (s != LBM_OK) return s;
-    if (bytes < lay.total) return fail(LBM_ERR_ARG, "workspace smaller than lbm_workspace_bytes()");
+    if (bytes < lay.min_total) return fail(LBM_ERR_ARG, "workspace smaller than lbm_workspace_bytes()");
     if ((uintptr_t)workspace % kAlign) return fail(LBM_ERR_ARG, "workspace must be 256-byte aligned");
     lbm_ctx_s *c = new (std::nothrow) lbm_ctx_s;
     if (!c) return fail(LBM_ERR_ARG, "out of host memory");
@@ -252,7 +293,7 @@ lbm_status lbm_init(const lbm_config *cfg, void *workspace, size_t bytes, void *
                  cfg->bc[2] == LBM_BOUNCEBACK, lay.plane, lay.cells};
     c->ws = (char *)workspace;
     c->lat[0] = c->ws;
-    c->lat[1] = lay.nlat == 2 ? c->ws + lay.lattice_bytes : nullptr;
+    c->lat[1] = lay.nlat == 2 ? c->ws + lay.lattice_bytes : (bytes >= lay.total && lay.multi ? c->ws + lay.stage_off : nullptr);
     c->part = (double *)(c->ws + lay.part_off);
     c->out = (double *)(c->ws + lay.out_off);
     c->block = cfg->block ? cfg->block : default_block(cfg->nx);
@@ -264,9 +305,20 @@ lbm_status lbm_init(const lbm_config *cfg, void *workspace, size_t bytes, void *
         for (int d = 0; d < 3; ++d) c->F[d] = cfg->force[d];
     }
     hipError_t e = hipSuccess;
-    if (c->lm) e = hipMemsetAsync(c->lm, 0, (size_t)lay.cells * sizeof(uint32_t), c->stream);  // no solids yet
+    c->multi = lay.multi && c->lat[1];
+    if (c->multi) {
+        int dev = 0, cus = 0;
+        e = hipGetDevice(&dev);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        c->plan = multi_plan(cfg->nx, cfg->ny, c->fp64, lay.porous || c->box.bbx || c->box.bby, lay.nlat == 2, cus);
+    }
+    if (e == hipSuccess && c->lm) e = hipMemsetAsync(c->lm, 0, (size_t)lay.cells * sizeof(uint32_t), c->stream);  // no solids yet
     if (e == hipSuccess)
         e = launch_init(m.lattice, c->fp64, c->lat[0], n0_dev, u0_dev, c->box, m, cfg->tau, c->rho_ref, c->block,
+                        c->stream);
+    // the slots of solid cells are never streamed into: both push lattices hold their initial values
+    if (e == hipSuccess && c->lm && lay.nlat == 2)
+        e = launch_init(m.lattice, c->fp64, c->lat[1], n0_dev, u0_dev, c->box, m, cfg->tau, c->rho_ref, c->block,
                         c->stream);
     if (e != hipSuccess) {
         delete c;
@@ -282,7 +334,7 @@ lbm_status lbm_step(lbm_ctx c, int64_t nsteps) {
     const int G = c->cfg.graph_steps;
     int64_t left = nsteps;
     while (G > 0 && left >= G) {
-        const int ph = phase(c);
+        const int ph = c->cur | parity(c);  // AA: cur is 0 between calls
         if (!c->graph[ph]) {
             lbm_status s = build_graph(c, ph);
             if (s != LBM_OK) return s;
@@ -292,17 +344,14 @@ lbm_status lbm_step(lbm_ctx c, int64_t nsteps) {
         c->steps += G;  // G even: the lattice index and the AA parity are unchanged
         left -= G;
     }
-    for (; left > 0; --left) {
-        hipError_t e = one_step(c, c->stream);
-        if (e != hipSuccess) return hip_fail(e, "step kernel launch");
-    }
-    return LBM_OK;
+    const hipError_t e = enqueue_steps(c, left, c->stream);
+    return e == hipSuccess ? LBM_OK : hip_fail(e, "step kernel launch");
 }
 
 lbm_status lbm_moments_device(lbm_ctx c, double *n_dev, double *u_dev) {
     if (!c || !n_dev || !u_dev) return fail(LBM_ERR_ARG, "null argument");
-    const int odd = c->cfg.scheme == LBM_SCHEME_AA ? (int)(c->steps & 1) : 0;
-    const void *lat = c->cfg.scheme == LBM_SCHEME_PUSH ? c->lat[c->cur] : c->lat[0];
+    const int odd = parity(c);
+    const void *lat = c->lat[c->cur];
     hipError_t e = launch_moments(c->model.lattice, c->fp64, lat, n_dev, u_dev, c->box, c->rho_ref, odd, c->block,
                                   c->lm, c->F, 0, c->lay.rows, c->lay.cells, c->stream);
     if (e != hipSuccess) return hip_fail(e, "moments kernel launch");
@@ -311,8 +360,8 @@ lbm_status lbm_moments_device(lbm_ctx c, double *n_dev, double *u_dev) {
 
 lbm_status lbm_moments(lbm_ctx c, double *n_host, double *u_host) {
     if (!c || !n_host || !u_host) return fail(LBM_ERR_ARG, "null argument");
-    const int odd = c->cfg.scheme == LBM_SCHEME_AA ? (int)(c->steps & 1) : 0;
-    const void *lat = c->cfg.scheme == LBM_SCHEME_PUSH ? c->lat[c->cur] : c->lat[0];
+    const int odd = parity(c);
+    const void *lat = c->lat[c->cur];
     const int D = c->model.D, nx = c->cfg.nx, rows = c->lay.rows, chunk = c->lay.stage_rows;
     const int64_t cells = c->lay.cells, cstride = (int64_t)chunk * nx;
     double *sn = (double *)(c->ws + c->lay.stage_off), *su = sn + cstride;
@@ -337,8 +386,8 @@ lbm_status lbm_moments(lbm_ctx c, double *n_host, double *u_host) {
 
 lbm_status lbm_totals(lbm_ctx c, double *out_host) {
     if (!c || !out_host) return fail(LBM_ERR_ARG, "null argument");
-    const int odd = c->cfg.scheme == LBM_SCHEME_AA ? (int)(c->steps & 1) : 0;
-    const void *lat = c->cfg.scheme == LBM_SCHEME_PUSH ? c->lat[c->cur] : c->lat[0];
+    const int odd = parity(c);
+    const void *lat = c->lat[c->cur];
     hipError_t e = launch_totals(c->model.lattice, c->fp64, lat, c->part, c->out, c->box, c->rho_ref, odd, c->block,
                                  c->lm, c->stream);
     if (e != hipSuccess) return hip_fail(e, "totals kernel launch");
@@ -425,8 +474,8 @@ lbm_status lbm_get_state(lbm_ctx c, void *host, size_t bytes) {
     if (!c || !host) return fail(LBM_ERR_ARG, "null argument");
     const size_t need = (size_t)c->model.Q * c->lay.cells * c->lay.elt;
     if (bytes != need) return fail(LBM_ERR_ARG, "state size mismatch");
-    const void *lat = c->cfg.scheme == LBM_SCHEME_PUSH ? c->lat[c->cur] : c->lat[0];
-    const bool odd = c->cfg.scheme == LBM_SCHEME_AA && (c->steps & 1);
+    const void *lat = c->lat[c->cur];
+    const bool odd = parity(c) != 0;
     std::vector<char> raw;
     void *dst = host;
     if (odd) {
@@ -454,8 +503,8 @@ lbm_status lbm_set_state(lbm_ctx c, const void *host, size_t bytes) {
     if (!c || !host) return fail(LBM_ERR_ARG, "null argument");
     const size_t need = (size_t)c->model.Q * c->lay.cells * c->lay.elt;
     if (bytes != need) return fail(LBM_ERR_ARG, "state size mismatch");
-    void *lat = c->cfg.scheme == LBM_SCHEME_PUSH ? c->lat[c->cur] : c->lat[0];
-    const bool odd = c->cfg.scheme == LBM_SCHEME_AA && (c->steps & 1);
+    void *lat = c->lat[c->cur];
+    const bool odd = parity(c) != 0;
     std::vector<char> raw;
     const void *src = host;
     hipError_t e = hipSuccess;

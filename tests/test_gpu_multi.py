@@ -1,0 +1,122 @@
+"""Calls of several steps on d2v9 boxes run as passes of several steps between two
+lattices (lbm_multi.hip).  Every cell update is the same arithmetic in the same
+order as in the single-step kernels, so one call of n steps must equal n calls of
+one step bit for bit: over strips and segments that end inside a box, boxes
+smaller than a strip, walls, solid cells with a force, both schemes and
+precisions, and the numbers of steps around each depth."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1510_07328_amd import inputs, lbm
+
+pytestmark = pytest.mark.gpu
+
+PUSH, AA = lbm.LBM_SCHEME_PUSH, lbm.LBM_SCHEME_AA
+
+
+def make(shape, bc=(0, 0, 0), porous=False, **kw):
+    nx, ny = shape
+    force = (2e-5, -1e-5, 0.0) if porous else (0.0, 0.0, 0.0)
+    cfg = lbm.make_config("d2v9", shape=(nx, ny, 1), bc=bc, tau=0.7, obstacles=int(porous), force=force, **kw)
+    n0, u0 = inputs.perturbed_field((ny, nx), 0.02, 3.0, (0.01, -0.02), seed=nx)
+    return cfg, n0, u0
+
+
+def solid_of(shape):
+    return inputs.porous_obstacles(shape, max(1, shape[0] * shape[1] // 300), 2.0, seed=3)
+
+
+def run(cfg, n0, u0, calls, solid=None):
+    lat = lbm.Lattice.create(cfg, n0, u0)
+    if solid is not None:
+        lat.set_solid(solid)
+    for n in calls:
+        lat.step(n)
+    out = lat.state(), lat.steps_done
+    n, u = lat.moments()
+    nh, uh = lat.moments_host()
+    torch.cuda.synchronize()
+    assert np.array_equal(nh, n.cpu().numpy()) and np.array_equal(uh, u.cpu().numpy())
+    lat.free()
+    return out
+
+
+@pytest.mark.parametrize("scheme", [PUSH, AA])
+@pytest.mark.parametrize("precision", [lbm.LBM_FP32_DEV, lbm.LBM_FP64])
+@pytest.mark.parametrize("shape,bc,porous,order", [
+    ((200, 90), (0, 0, 0), False, 2),    # several strips, the last one cut
+    ((61, 50), (0, 0, 0), False, 3),     # one strip and a part of one
+    ((5, 3), (0, 0, 0), False, 2),       # a strip wraps round the box many times
+    ((1, 64), (0, 0, 0), False, 2),
+    ((131, 1), (1, 0, 0), False, 2),
+    ((131, 40), (1, 0, 0), False, 2),    # walls in x, in y, in both
+    ((60, 33), (0, 1, 0), False, 2),
+    ((58, 9), (1, 1, 0), False, 3),
+    ((150, 70), (0, 0, 0), True, 2),     # solid cells and a force, without and with walls
+    ((77, 41), (1, 1, 0), True, 3),
+])
+def test_one_call_of_n_steps_equals_n_calls(gpu, shape, bc, porous, order, precision, scheme):
+    cfg, n0, u0 = make(shape, bc, porous, order=order, precision=precision, scheme=scheme)
+    solid = solid_of(shape) if porous else None
+    for n in (2, 3, 4, 5, 6, 7, 8, 10, 13, 14, 25):
+        one, s1 = run(cfg, n0, u0, [1] * n, solid)
+        for calls in ([n], [1, n - 1], [n - 1, 1]):
+            many, s2 = run(cfg, n0, u0, calls, solid)
+            assert s1 == s2 == n
+            assert np.array_equal(one, many), (n, calls, int((one != many).sum()))
+
+
+@pytest.mark.parametrize("scheme", [PUSH, AA])
+def test_large_boxes_take_deep_passes(gpu, scheme):
+    """A box whose plan is the deepest pass (several wavefronts per SIMD), ragged against strips and segments."""
+    cfg, n0, u0 = make((2111, 1537), order=2, scheme=scheme)
+    one, _ = run(cfg, n0, u0, [1] * 26)
+    many, _ = run(cfg, n0, u0, [26])
+    assert np.array_equal(one, many)
+
+
+def test_aa_runs_in_a_workspace_of_one_lattice(gpu):
+    """A caller that gives an AA box no second lattice still gets its steps, in place."""
+    cfg, n0, u0 = make((200, 90), order=2, scheme=AA)
+    full = lbm.lbm_workspace_bytes(cfg)
+    lattice = 9 * (200 * 90 + 8448 // 4) * 4
+    stage = 3 * 8 * 200 * 90  # the whole box is staged at once by the host moments
+    small = full - (lattice + 255) // 256 * 256 + (stage + 255) // 256 * 256
+    assert small < full
+    n = torch.as_tensor(n0).cuda()
+    u = torch.as_tensor(u0).cuda().contiguous()
+    ws = torch.empty(small, dtype=torch.uint8, device="cuda")
+    ctx = lbm.lbm_init(cfg, ws.data_ptr(), small, torch.cuda.current_stream().cuda_stream, n.data_ptr(), u.data_ptr())
+    lbm.lbm_step(ctx, 13)
+    got = np.empty((9, 200 * 90), dtype=np.float32)
+    lbm.lbm_get_state(ctx, got.ctypes.data, got.nbytes)
+    lbm.lbm_free(ctx)
+    ref, _ = run(cfg, n0, u0, [1] * 13)
+    assert np.array_equal(ref, got)
+    with pytest.raises(lbm.LbmError):
+        lbm.lbm_init(cfg, ws.data_ptr(), small - 256, torch.cuda.current_stream().cuda_stream, n.data_ptr(),
+                     u.data_ptr())
+
+
+@pytest.mark.parametrize("scheme", [PUSH, AA])
+@pytest.mark.parametrize("n", [2, 6, 10])
+def test_a_captured_call_can_be_replayed(gpu, scheme, n):
+    """An even number of steps ends in the lattice it started from, so a caller's own graph of the
+    call advances the state on every replay."""
+    cfg, n0, u0 = make((150, 60), order=2, scheme=scheme)
+    side = torch.cuda.Stream()
+    lat = lbm.Lattice.create(cfg, n0, u0, stream=side)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        lat.step(n)
+    for k in range(1, 5):
+        g.replay()
+        torch.cuda.synchronize()
+        got = lat.state()
+        ref, _ = run(cfg, n0, u0, [1] * (n * k))
+        assert np.array_equal(ref, got), k
+    lat.free()

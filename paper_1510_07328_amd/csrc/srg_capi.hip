@@ -29,21 +29,20 @@ hipError_t batch_rounds_dev(lbm_batch_s *b);
 namespace srg {
 hipError_t l1_fwd(const float *nu, const float *tau, const __bf16 *W1, const float *b1, __bf16 *z1, __bf16 *a1, int B,
                   int L, hipStream_t s);
-hipError_t hidden(bool dgrad, const __bf16 *in, const __bf16 *Wop, const float *bias, const __bf16 *zprev,
-                  __bf16 *out_z, __bf16 *out_a, int B, int L, int d, hipStream_t s);
-hipError_t hidden_wgrad(const __bf16 *dz, const __bf16 *a, float *part, float *partb, int G, int B, int L, int d,
-                        hipStream_t s);
+hipError_t hidden(const __bf16 *in, const __bf16 *Wop, const float *bias, __bf16 *out_z, __bf16 *out_a, int B, int L,
+                  int d, hipStream_t s);
 hipError_t l4_fwd(const __bf16 *a3, const __bf16 *W4, const float *b4, const float *nu, float *out, int B, int L,
                   hipStream_t s);
 hipError_t fwd_fused(const float *nu, const float *tau, const __bf16 *W1, const float *b1, const __bf16 *W2,
                      const float *b2, const __bf16 *W3, const float *b3, const __bf16 *W4, const float *b4, float *out,
-                     int B, int L, hipStream_t s);
+                     __bf16 *z1, __bf16 *z2, __bf16 *z3, int B, int L, hipStream_t s);
 int fused_max_length();
-hipError_t l4_dgrad(const float *dout, const __bf16 *W4, const __bf16 *z3, __bf16 *dz3, int B, int L, hipStream_t s);
-hipError_t l4_wgrad(const float *dout, const __bf16 *a3, float *part, int G, int B, int L, hipStream_t s);
-hipError_t l1_wgrad(const __bf16 *dz1, const float *nu, const float *tau, float *part, int G, int B, int L,
-                    hipStream_t s);
-hipError_t reduce(const float *part, int G, int n, float *dst, hipStream_t s);
+hipError_t bwd_out(const float *dout, const __bf16 *W4, const __bf16 *z3, __bf16 *dz3, float *part, int G, int B,
+                   int L, hipStream_t s);
+hipError_t bwd_hidden(int d, const __bf16 *dz, const __bf16 *zp, const __bf16 *Wt, __bf16 *dzp, float *part,
+                      const float *nu, const float *tau, float *part1, int G, int B, int L, hipStream_t s);
+hipError_t reduce(const float *const (&part)[4], const int (&groups)[4], const int (&n)[4], const int (&dst)[4],
+                  float *grad, hipStream_t s);
 hipError_t loss(const float *out, const float *target, float *dout, float *stats, int B, int L, float lambda,
                 hipStream_t s);
 hipError_t mass_residual(const float *in, const float *out, float *resid, int B, int L, hipStream_t s);
@@ -61,7 +60,8 @@ constexpr int CH = 64, KT = 5;
 constexpr int NW1 = KT * CH * 3, NW2 = KT * CH * CH, NW4 = KT * 2 * CH;
 constexpr int OW1 = 0, OB1 = OW1 + NW1, OW2 = OB1 + CH, OB2 = OW2 + NW2, OW3 = OB2 + CH, OB3 = OW3 + NW2,
               OW4 = OB3 + CH, OB4 = OW4 + NW4, NPARAM = OB4 + 2;
-constexpr int G = 256;  // workgroups of the weight-gradient reductions
+constexpr int G = 256, G4 = 512;  // most workgroups of the backward kernels of layers 2 and 3, and of layer 4
+constexpr int TB = 128;           // positions per tile of those kernels
 constexpr int DIL[4] = {1, 3, 9, 27};
 constexpr int NCOUNT = 1024;  // fallback counts kept on the device between read-backs
 
@@ -86,7 +86,7 @@ struct Carve {
 };
 
 struct Offsets {
-    size_t master, m, v, grad, w1b, w2b, w2t, w3b, w3t, w4b, act[6], dz[3], part, partb, part4, part1, dout, stats,
+    size_t master, m, v, grad, w1b, w2b, w2t, w3b, w3t, w4b, z[3], a[3], dz[2], part3, part2, part4, part1, dout, stats,
         resid, counts, prof_in, prof_out, lazy, total;
 };
 
@@ -104,12 +104,14 @@ Offsets layout(int B, int L) {
     o.w3t = c.take<__bf16>(NW2);
     o.w4b = c.take<__bf16>(NW4);
     const size_t act = (size_t)B * L * CH;
-    for (auto &a : o.act) a = c.take<__bf16>(act);
-    for (auto &a : o.dz) a = c.take<__bf16>(act);
-    o.part = c.take<float>((size_t)G * NW2);
-    o.partb = c.take<float>((size_t)G * CH);
-    o.part4 = c.take<float>((size_t)G * (NW4 + 2));
-    o.part1 = c.take<float>((size_t)G * (NW1 + CH));
+    for (auto &z : o.z) z = c.take<__bf16>(act);
+    for (auto &a : o.a) a = L > srg::fused_max_length() ? c.take<__bf16>(act) : 0;  // layer by layer only
+    for (auto &d : o.dz) d = c.take<__bf16>(act);
+    const size_t tiles = (size_t)B * (L / TB), g = tiles < (size_t)G ? tiles : G, g4 = tiles < (size_t)G4 ? tiles : G4;
+    o.part3 = c.take<float>(g * (NW2 + CH));
+    o.part2 = c.take<float>(g * (NW2 + CH));
+    o.part4 = c.take<float>(g4 * (NW4 + 2));
+    o.part1 = c.take<float>(g * (NW1 + CH));
     o.dout = c.take<float>((size_t)B * 2 * L);
     o.stats = c.take<float>((size_t)B * 2);
     o.resid = c.take<float>((size_t)B);
@@ -150,61 +152,50 @@ hipError_t prepare_weights(srg_ctx_s *c) {
     return e;
 }
 
-// keep = true: layer by layer, the activations (and pre-activations z) kept for
-// a backward pass; keep = false: inference, all layers in one kernel for lengths
-// up to srg::fused_max_length() (the same result bit for bit, nothing kept),
-// layer by layer without the z beyond
+// keep = true: the pre-activations z kept for a backward pass.  All layers in one
+// kernel for lengths up to srg::fused_max_length(), layer by layer beyond (the
+// same result bit for bit).
 hipError_t forward(srg_ctx_s *c, const float *nu, const float *tau, int B, float *out, bool keep) {
     const int L = c->L;
     const float *p = c->at<float>(c->o.master);
-    if (!keep && L <= srg::fused_max_length()) {
-        c->lastB = 0;
-        return srg::fwd_fused(nu, tau, c->at<__bf16>(c->o.w1b), p + OB1, c->at<__bf16>(c->o.w2b), p + OB2,
-                              c->at<__bf16>(c->o.w3b), p + OB3, c->at<__bf16>(c->o.w4b), p + OB4, out, B, L, c->stream);
+    __bf16 *z1 = nullptr, *z2 = nullptr, *z3 = nullptr;
+    if (keep) {
+        z1 = c->at<__bf16>(c->o.z[0]);
+        z2 = c->at<__bf16>(c->o.z[1]);
+        z3 = c->at<__bf16>(c->o.z[2]);
     }
-    __bf16 *z1 = c->at<__bf16>(c->o.act[0]), *a1 = c->at<__bf16>(c->o.act[1]);
-    __bf16 *z2 = c->at<__bf16>(c->o.act[2]), *a2 = c->at<__bf16>(c->o.act[3]);
-    __bf16 *z3 = c->at<__bf16>(c->o.act[4]), *a3 = c->at<__bf16>(c->o.act[5]);
-    if (!keep) z1 = z2 = z3 = nullptr;
-    hipError_t e = srg::l1_fwd(nu, tau, c->at<__bf16>(c->o.w1b), p + OB1, z1, a1, B, L, c->stream);
-    if (e == hipSuccess)
-        e = srg::hidden(false, a1, c->at<__bf16>(c->o.w2b), p + OB2, nullptr, z2, a2, B, L, DIL[1], c->stream);
-    if (e == hipSuccess)
-        e = srg::hidden(false, a2, c->at<__bf16>(c->o.w3b), p + OB3, nullptr, z3, a3, B, L, DIL[2], c->stream);
-    if (e == hipSuccess) e = srg::l4_fwd(a3, c->at<__bf16>(c->o.w4b), p + OB4, nu, out, B, L, c->stream);
     c->lastB = keep ? B : 0;
     c->last_nu = nu;
     c->last_tau = tau;
+    if (L <= srg::fused_max_length())
+        return srg::fwd_fused(nu, tau, c->at<__bf16>(c->o.w1b), p + OB1, c->at<__bf16>(c->o.w2b), p + OB2,
+                              c->at<__bf16>(c->o.w3b), p + OB3, c->at<__bf16>(c->o.w4b), p + OB4, out, z1, z2, z3, B, L,
+                              c->stream);
+    __bf16 *a1 = c->at<__bf16>(c->o.a[0]), *a2 = c->at<__bf16>(c->o.a[1]), *a3 = c->at<__bf16>(c->o.a[2]);
+    hipError_t e = srg::l1_fwd(nu, tau, c->at<__bf16>(c->o.w1b), p + OB1, z1, a1, B, L, c->stream);
+    if (e == hipSuccess) e = srg::hidden(a1, c->at<__bf16>(c->o.w2b), p + OB2, z2, a2, B, L, DIL[1], c->stream);
+    if (e == hipSuccess) e = srg::hidden(a2, c->at<__bf16>(c->o.w3b), p + OB3, z3, a3, B, L, DIL[2], c->stream);
+    if (e == hipSuccess) e = srg::l4_fwd(a3, c->at<__bf16>(c->o.w4b), p + OB4, nu, out, B, L, c->stream);
     return e;
 }
 
 hipError_t backward(srg_ctx_s *c, const float *dout, float *grad) {
-    const int B = c->lastB, L = c->L;
-    __bf16 *z1 = c->at<__bf16>(c->o.act[0]), *a1 = c->at<__bf16>(c->o.act[1]);
-    __bf16 *z2 = c->at<__bf16>(c->o.act[2]), *a2 = c->at<__bf16>(c->o.act[3]);
-    __bf16 *z3 = c->at<__bf16>(c->o.act[4]), *a3 = c->at<__bf16>(c->o.act[5]);
-    __bf16 *dz3 = c->at<__bf16>(c->o.dz[2]), *dz2 = c->at<__bf16>(c->o.dz[1]), *dz1 = c->at<__bf16>(c->o.dz[0]);
-    float *part = c->at<float>(c->o.part), *partb = c->at<float>(c->o.partb);
-    float *part4 = c->at<float>(c->o.part4), *part1 = c->at<float>(c->o.part1);
-    const int g = B < G ? B : G;
-    hipError_t e = srg::l4_wgrad(dout, a3, part4, g, B, L, c->stream);
-    if (e == hipSuccess) e = srg::reduce(part4, g, NW4 + 2, grad + OW4, c->stream);  // W4 then b4 (contiguous)
-    if (e == hipSuccess) e = srg::l4_dgrad(dout, c->at<__bf16>(c->o.w4b), z3, dz3, B, L, c->stream);
-    // layer 3: weights, then the data gradient into layer 2's dz
-    if (e == hipSuccess) e = srg::hidden_wgrad(dz3, a2, part, partb, g, B, L, DIL[2], c->stream);
-    if (e == hipSuccess) e = srg::reduce(part, g, NW2, grad + OW3, c->stream);
-    if (e == hipSuccess) e = srg::reduce(partb, g, CH, grad + OB3, c->stream);
+    const int B = c->lastB, L = c->L, tiles = B * (L / TB);
+    const int g = tiles < G ? tiles : G, g4 = tiles < G4 ? tiles : G4;
+    __bf16 *z1 = c->at<__bf16>(c->o.z[0]), *z2 = c->at<__bf16>(c->o.z[1]), *z3 = c->at<__bf16>(c->o.z[2]);
+    __bf16 *dz3 = c->at<__bf16>(c->o.dz[1]), *dz2 = c->at<__bf16>(c->o.dz[0]);
+    float *part1 = c->at<float>(c->o.part1), *part2 = c->at<float>(c->o.part2);
+    float *part3 = c->at<float>(c->o.part3), *part4 = c->at<float>(c->o.part4);
+    hipError_t e = srg::bwd_out(dout, c->at<__bf16>(c->o.w4b), z3, dz3, part4, g4, B, L, c->stream);
     if (e == hipSuccess)
-        e = srg::hidden(true, dz3, c->at<__bf16>(c->o.w3t), nullptr, z2, dz2, nullptr, B, L, DIL[2], c->stream);
-    // layer 2
-    if (e == hipSuccess) e = srg::hidden_wgrad(dz2, a1, part, partb, g, B, L, DIL[1], c->stream);
-    if (e == hipSuccess) e = srg::reduce(part, g, NW2, grad + OW2, c->stream);
-    if (e == hipSuccess) e = srg::reduce(partb, g, CH, grad + OB2, c->stream);
+        e = srg::bwd_hidden(DIL[2], dz3, z2, c->at<__bf16>(c->o.w3t), dz2, part3, nullptr, nullptr, nullptr, g, B, L,
+                            c->stream);
     if (e == hipSuccess)
-        e = srg::hidden(true, dz2, c->at<__bf16>(c->o.w2t), nullptr, z1, dz1, nullptr, B, L, DIL[1], c->stream);
-    // layer 1 (weights only)
-    if (e == hipSuccess) e = srg::l1_wgrad(dz1, c->last_nu, c->last_tau, part1, g, B, L, c->stream);
-    if (e == hipSuccess) e = srg::reduce(part1, g, NW1 + CH, grad + OW1, c->stream);  // W1 then b1 (contiguous)
+        e = srg::bwd_hidden(DIL[1], dz2, z1, c->at<__bf16>(c->o.w2t), nullptr, part2, c->last_nu, c->last_tau, part1, g,
+                            B, L, c->stream);
+    if (e == hipSuccess)  // each layer's biases follow its weights
+        e = srg::reduce({part1, part2, part3, part4}, {g, g, g, g4}, {NW1 + CH, NW2 + CH, NW2 + CH, NW4 + 2},
+                        {OW1, OW2, OW3, OW4}, grad, c->stream);
     return e;
 }
 
@@ -473,6 +464,6 @@ extern "C" lbm_status srg_infer_noalloc(const float *params_dev, const float *pr
     if (e == hipSuccess) e = srg::to_bf16(params_dev + OW4, w4, NW4, s);
     if (e == hipSuccess)
         e = srg::fwd_fused(prof_dev, tau_dev, w1, params_dev + OB1, w2, params_dev + OB2, w3, params_dev + OB3, w4,
-                           params_dev + OB4, out_dev, batch, length, s);
+                           params_dev + OB4, out_dev, nullptr, nullptr, nullptr, batch, length, s);
     return e == hipSuccess ? LBM_OK : shipf(e, "srg_infer_noalloc");
 }

@@ -9,165 +9,11 @@
 // (from float32 master copies), accumulation float32.  The two 64->64 layers
 // (97% of the flops) run on the bf16 matrix cores: a workgroup computes a 64
 // (positions) x 64 (channels) tile as four 32x32 blocks, one per wavefront, with
-// v_mfma_f32_32x32x16_bf16 over K = 5 taps x 64 channels.  The data-gradient of
-// a layer is the same kernel with the taps reversed and the weights transposed;
-// the weight-gradient is a K = positions reduction, per workgroup into float32
-// partials that a second kernel sums in a fixed order.  The 3->64 and 64->2
-// layers are too thin for the matrix cores and use plain FMA.
-#include <hip/hip_runtime.h>
-
-#include <cstdint>
-#include <mutex>
-#include <type_traits>
+// v_mfma_f32_32x32x16_bf16 over K = 5 taps x 64 channels.  The backward pass is in
+// srg_backward.hip.
+#include "srg_common.h"
 
 namespace srg {
-
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
-
-constexpr int CH = 64;
-constexpr int KT = 5;
-constexpr float FS = 0.25f;       // feature scale
-constexpr float TAU_C = 0.75f;    // tau centre
-
-// erf by Abramowitz & Stegun, Handbook of Mathematical Functions (1964), formula
-// 7.1.26 (Hastings' approximation): for x >= 0,
-//   erf(x) = 1 - t (a1 + t (a2 + t (a3 + t (a4 + t a5)))) exp(-x^2),  t = 1 / (1 + p x),
-// with an absolute error of at most 1.5e-7 (far below the bfloat16 rounding the
-// activations then take); odd extension for x < 0.  exp(-x^2) is shared with GELU'.
-struct ErfExp {
-    float erf, e;  // erf(x) and exp(-x^2)
-};
-__device__ __forceinline__ ErfExp erf_exp(float x) {
-    const float ax = __builtin_fabsf(x);
-    const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3275911f, ax, 1.0f));
-    float p = __builtin_fmaf(1.061405429f, t, -1.453152027f);
-    p = __builtin_fmaf(p, t, 1.421413741f);
-    p = __builtin_fmaf(p, t, -0.284496736f);
-    p = __builtin_fmaf(p, t, 0.254829592f);
-    const float e = __builtin_amdgcn_exp2f(-ax * ax * 1.4426950408889634f);
-    const float r = __builtin_fmaf(-p * t, e, 1.0f);
-    return {__builtin_copysignf(r, x), e};
-}
-// GELU(z) = z Phi(z) = z (1 + erf(z / sqrt 2)) / 2
-__device__ __forceinline__ float gelu(float z) {
-    return 0.5f * z * (1.0f + erf_exp(z * 0.70710678118654752f).erf);
-}
-// GELU'(z) = Phi(z) + z phi(z), phi(z) = exp(-z^2 / 2) / sqrt(2 pi)
-__device__ __forceinline__ float gelu_grad(float z) {
-    const ErfExp q = erf_exp(z * 0.70710678118654752f);
-    return __builtin_fmaf(z * 0.39894228040143268f, q.e, 0.5f * (1.0f + q.erf));
-}
-__device__ __forceinline__ __bf16 to_bf(float v) { return (__bf16)v; }
-__device__ __forceinline__ float to_f(__bf16 v) { return (float)v; }
-
-// bf16(GELU(z)) for a bfloat16 z by table: the forward rounds z to bfloat16
-// before the GELU, so the result is a function of 16 bits.  A table covers the
-// NE biased exponents E0 .. E0 + NE - 1 of both signs (2 NE 128 entries) and is
-// written by gelu() itself, so a lookup gives the bits the computation gives;
-// values outside it (smaller or larger magnitudes, zero, non-finite) are
-// computed.  GeluT16: |z| in [2^-12, 16), 4096 entries, 8 KB of LDS (the layer-1
-// kernel); GeluT32: |z| in [2^-24, 128), 8192 entries, 16 KB (the fused kernel,
-// where a wavefront takes the computed path for all its values as soon as one
-// lane holds a value outside the table: with the trained weights about 1 % of
-// the pre-activations of layers 1-2 lie below 2^-12, and on strong shocks up to
-// 17 % of layer 3's reach 16 and beyond (up to 62), so that with the smaller
-// table nearly every wavefront took that path).
-template <int E0, int NE>
-struct GeluTable {
-    static constexpr int HALF = NE * 128, N = 2 * HALF, BIAS = E0 << 7;
-    static_assert(HALF == 0x800 || HALF == 0x1000, "the index's sign bit is bit 11 or 12");
-    static __device__ __forceinline__ unsigned short entry(int i) {
-        const unsigned bits = ((unsigned)(i / HALF) << 15) | (unsigned)((E0 << 7) + i % HALF);
-        const __bf16 z = __builtin_bit_cast(__bf16, (unsigned short)bits);
-        return __builtin_bit_cast(unsigned short, to_bf(gelu(to_f(z))));
-    }
-    static __device__ __forceinline__ bool lookup(__bf16 z, unsigned *index) {
-        const unsigned bits = __builtin_bit_cast(unsigned short, z);
-        const unsigned t = (bits & 0x7fffu) - (unsigned)(E0 << 7);
-        *index = t + (bits >> 15) * HALF;
-        return t < (unsigned)HALF;
-    }
-};
-using GeluT16 = GeluTable<115, 16>;
-using GeluT32 = GeluTable<103, 32>;
-
-// GELU of bfloat16 pairs (32-bit words, low half first) by table, the index
-// formed by 16-bit packed operations: per half t = (z & 0x7fff) - (E0 << 7), in
-// the table when t < HALF, entry t + HALF sign.
-typedef unsigned short us2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ unsigned pack_bf2(float x, float y) {
-    const bf16x2 v = {to_bf(x), to_bf(y)};
-    return __builtin_bit_cast(unsigned, v);
-}
-// t of both halves
-template <class Tab>
-__device__ __forceinline__ unsigned gelu_bf2_t(unsigned z) {
-    return __builtin_bit_cast(unsigned, __builtin_bit_cast(us2, z & 0x7fff7fffu) - (us2)((unsigned short)Tab::BIAS));
-}
-// v[i] from the table for every value, every read issued before any result is
-// used; the index is taken within the table, so a value outside it reads some
-// entry and must be replaced (gelu_bf2_outside, gelu_bf2_word)
-template <class Tab, int N>
-__device__ __forceinline__ void gelu_bf2_table(const unsigned (&z)[N], unsigned (&v)[N], const unsigned short *tab) {
-    constexpr unsigned H = Tab::HALF;
-    constexpr unsigned LOW = (H - 1u) * 0x10001u;  // t within the table
-    constexpr unsigned SIGN = H * 0x10001u;        // the index's sign bit
-    constexpr unsigned SH = H == 0x800 ? 4u : 3u;  // bit 15 -> that bit
-    const char *tb = reinterpret_cast<const char *>(tab);
-    us2 e[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const unsigned idx = (gelu_bf2_t<Tab>(z[i]) & LOW) | ((z[i] >> SH) & SIGN);
-        const unsigned off = __builtin_bit_cast(unsigned, __builtin_bit_cast(us2, idx) << (us2)(1));
-        e[i].x = *reinterpret_cast<const unsigned short *>(tb + (off & 0xffffu));
-        e[i].y = *reinterpret_cast<const unsigned short *>(tb + (off >> 16));
-    }
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = __builtin_bit_cast(unsigned, e[i]);
-}
-// nonzero when some value of z lies outside the table
-template <class Tab, int N>
-__device__ __forceinline__ unsigned gelu_bf2_outside(const unsigned (&z)[N]) {
-    unsigned any = 0u;
-#pragma unroll
-    for (int i = 0; i < N; ++i) any |= gelu_bf2_t<Tab>(z[i]);
-    return any & ((0x10000u - Tab::HALF) * 0x10001u);
-}
-// one word, each half from the table or computed
-template <class Tab>
-__device__ __forceinline__ unsigned gelu_bf2_word(unsigned z, const unsigned short *tab) {
-    unsigned short r[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const __bf16 zh = __builtin_bit_cast(__bf16, (unsigned short)(z >> (16 * h)));
-        unsigned idx;
-        r[h] = Tab::lookup(zh, &idx) ? tab[idx] : __builtin_bit_cast(unsigned short, to_bf(gelu(to_f(zh))));
-    }
-    return r[0] | ((unsigned)r[1] << 16);
-}
-// v[i] = bf16(GELU(.)) of z[i]: the table when no lane of the wave holds a value
-// outside it, else each value from the table or computed
-template <class Tab, int N>
-__device__ __forceinline__ void gelu_bf2_n(const unsigned (&z)[N], unsigned (&v)[N], const unsigned short *tab) {
-    if (__builtin_amdgcn_ballot_w64(gelu_bf2_outside<Tab>(z) != 0u) == 0) {
-        gelu_bf2_table<Tab>(z, v, tab);
-    } else {
-#pragma unroll
-        for (int i = 0; i < N; ++i) v[i] = gelu_bf2_word<Tab>(z[i], tab);
-    }
-}
-
-// feature channel ci at position x of sample b (zero outside [0, L))
-__device__ __forceinline__ float feature(const float *__restrict__ nu, const float *__restrict__ tau, int b, int L,
-                                         int ci, int x) {
-    if (x < 0 || x >= L) return 0.0f;
-    if (ci == 0) return (nu[(int64_t)b * 2 * L + x] - 1.0f) / FS;
-    if (ci == 1) return nu[(int64_t)b * 2 * L + L + x] / FS;
-    return (tau[b] - TAU_C) / FS;
-}
 
 // ---------------------------------------------------------------------------
 // layer 1: 3 -> 64, dilation 1, on the matrix cores.  A 16 x 16 block (16
@@ -186,7 +32,6 @@ __device__ __forceinline__ float feature(const float *__restrict__ nu, const flo
 // kernel's bit for bit.
 // ---------------------------------------------------------------------------
 constexpr int P1F = 256;
-constexpr int RS = CH + 8;  // LDS row stride of a 64-channel activation row, in elements (144 bytes)
 // feature slots of a lane group: (feature channel, tap) with channel 3 = the bias slot
 __device__ __forceinline__ int l1_slot_ch(int s, int j) { return s == 0 ? (j < 5 ? 0 : 1) : (j < 2 ? 1 : (j == 2 ? 3 : 2)); }
 __device__ __forceinline__ int l1_slot_tap(int s, int j) { return s == 0 ? (j < 5 ? j : j - 5) : (j < 2 ? 3 + j : (j == 2 ? 0 : j - 3)); }
@@ -237,7 +82,7 @@ __global__ void __launch_bounds__(256) k_l1_fwd(const float *__restrict__ nu, co
         const int c = i / (P1F + 4), k = i % (P1F + 4);
         fs[c][k] = feature(nu, tau, b, L, c, x0 - 2 + k);
     }
-    for (int i = threadIdx.x; i < GeluT16::N; i += blockDim.x) gt[i] = GeluT16::entry(i);
+    GeluT16::fill(gt);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lc = lane & 15, g = lane >> 4, s = g >> 1;
     bf16x8 wa[4];
 #pragma unroll
@@ -283,12 +128,9 @@ __global__ void __launch_bounds__(256) k_l1_fwd(const float *__restrict__ nu, co
 }
 
 // ---------------------------------------------------------------------------
-// 64 -> 64 layers on the matrix cores.
-//   forward (DGRAD = false): out[x, n] = bias[n] + sum_{tap,k} in[x + (tap-2)d, k] Wop[tap][n][k];
-//     stores a = bf16(GELU(z)) with z = bf16(out), and z itself when out_z is not null.
-//   data gradient (DGRAD = true): out[x, n] = sum_{tap,k} in[x - (tap-2)d, k] Wop[tap][n][k]
-//     with in = dz of the layer above and Wop the transposed weights; stores
-//     dz_prev = bf16(out * GELU'(zprev[x, n])) into out_z.
+// 64 -> 64 layers on the matrix cores (profiles longer than the one-kernel
+// forward takes): out[x, n] = bias[n] + sum_{tap,k} in[x + (tap-2)d, k] Wop[tap][n][k];
+// stores a = bf16(GELU(z)) with z = bf16(out), and z itself when out_z is not null.
 // A workgroup keeps the layer's weights in LDS and walks tiles of TM = 128
 // positions (b, x0) with stride gridDim.x; each of its 4 wavefronts computes 32
 // positions x 64 channels as two 32 x 32 blocks (v_mfma_f32_32x32x16_bf16, K =
@@ -297,16 +139,14 @@ __global__ void __launch_bounds__(256) k_l1_fwd(const float *__restrict__ nu, co
 // through LDS and leave as 16-byte row stores.
 // ---------------------------------------------------------------------------
 constexpr int TM = 128;
-constexpr int RSF = CH + 4;  // row stride of the float32 results of the data gradient (272 bytes)
 
-template <bool DGRAD>
 __global__ void __launch_bounds__(256) k_hidden(const __bf16 *__restrict__ in, const __bf16 *__restrict__ Wop,
-                                                const float *__restrict__ bias, const __bf16 *__restrict__ zprev,
+                                                const float *__restrict__ bias,
                                                 __bf16 *__restrict__ out_z, __bf16 *__restrict__ out_a, int B, int L,
                                                 int d) {
     extern __shared__ unsigned char smem[];
     __bf16 *wl = reinterpret_cast<__bf16 *>(smem);  // [5 * 64][RS]
-    __bf16 *tile = wl + KT * CH * RS;  // [TM + 4d][RS] input rows, then the results ([TM][RS] bf16 or [TM][RSF] float)
+    __bf16 *tile = wl + KT * CH * RS;  // [TM + 4d][RS] input rows, then the results [TM][RS]
     for (int i = threadIdx.x; i < KT * CH * (CH / 8); i += blockDim.x)
         *(bf16x8 *)(wl + (i >> 3) * RS + 8 * (i & 7)) = ((const bf16x8 *)Wop)[i];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -342,16 +182,14 @@ __global__ void __launch_bounds__(256) k_hidden(const __bf16 *__restrict__ in, c
         __syncthreads();
         if (t + (int)gridDim.x < ntiles) fetch(t + gridDim.x);
         floatx16 acc0 = {}, acc1 = {};
-        if (!DGRAD) {  // the forward sums start from the bias
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                acc0[r] = bias[lr];
-                acc1[r] = bias[32 + lr];
-            }
+        for (int r = 0; r < 16; ++r) {  // the sums start from the bias
+            acc0[r] = bias[lr];
+            acc1[r] = bias[32 + lr];
         }
 #pragma unroll
         for (int tap = 0; tap < KT; ++tap) {
-            const int off = (DGRAD ? (KT - 1 - tap) : tap) * d;
+            const int off = tap * d;
             const __bf16 *arow = tile + (m0 + lr + off) * RS + lk;
             const __bf16 *b0row = wl + (tap * CH + lr) * RS + lk;
             const __bf16 *b1row = b0row + 32 * RS;
@@ -366,142 +204,24 @@ __global__ void __launch_bounds__(256) k_hidden(const __bf16 *__restrict__ in, c
         }
         __syncthreads();  // every wavefront is done reading the input tile
         // D[i][j]: i = 8 (r / 4) + 4 (lane / 32) + r % 4 (position), j = lane % 32 (channel)
-        if (!DGRAD) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int pl = m0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                tile[pl * RS + lr] = to_bf(acc0[r]);
-                tile[pl * RS + 32 + lr] = to_bf(acc1[r]);
-            }
-        } else {
-            // float32 results (row stride 68 floats) so that GELU'(zprev) is applied
-            // before the one rounding, with zprev read as whole rows below
-            float *res = reinterpret_cast<float *>(tile);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int pl = m0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                res[pl * RSF + lr] = acc0[r];
-                res[pl * RSF + 32 + lr] = acc1[r];
-            }
+        for (int r = 0; r < 16; ++r) {
+            const int pl = m0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            tile[pl * RS + lr] = to_bf(acc0[r]);
+            tile[pl * RS + 32 + lr] = to_bf(acc1[r]);
         }
         __syncthreads();
         for (int i = threadIdx.x; i < TM * (CH / 8); i += blockDim.x) {
             const int p = i >> 3, v = i & 7;
             const int64_t row = ((int64_t)b * L + x0 + p) * CH + 8 * v;
-            if (!DGRAD) {
-                const bf16x8 zv = *(const bf16x8 *)(tile + p * RS + 8 * v);
-                if (out_z) *(bf16x8 *)(out_z + row) = zv;
-                bf16x8 av;
+            const bf16x8 zv = *(const bf16x8 *)(tile + p * RS + 8 * v);
+            if (out_z) *(bf16x8 *)(out_z + row) = zv;
+            bf16x8 av;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) av[j] = to_bf(gelu(to_f(zv[j])));
-                *(bf16x8 *)(out_a + row) = av;
-            } else {
-                const float *res = reinterpret_cast<const float *>(tile) + p * RSF + 8 * v;
-                const bf16x8 zp = *(const bf16x8 *)(zprev + row);
-                bf16x8 dv;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) dv[j] = to_bf(res[j] * gelu_grad(to_f(zp[j])));
-                *(bf16x8 *)(out_z + row) = dv;
-            }
+            for (int j = 0; j < 8; ++j) av[j] = to_bf(gelu(to_f(zv[j])));
+            *(bf16x8 *)(out_a + row) = av;
         }
     }
-}
-
-// ---------------------------------------------------------------------------
-// weight gradient of a 64 -> 64 layer on the matrix cores:
-//   dW[tap][co][ci] = sum_{b, x} dz[b, x, co] a[b, x + (tap-2) D, ci],  db[co] = sum dz[b, x, co].
-// Workgroup g takes samples g, g + G, ...; chunks of TW positions are staged in
-// LDS channel-major (each lane's 8 consecutive positions contiguous).  Staging
-// lanes take consecutive positions of one 8-channel group, so the transposing
-// 2-byte stores of a wave land in consecutive LDS words.  The shifted operand
-// a[x + (tap-2) D] starts at an odd element for odd tap * D; a second copy of
-// the a tile shifted by one element keeps every operand read 4-byte aligned.
-// Output: float32 partials part[g][5][64][64] and partb[g][64].
-// ---------------------------------------------------------------------------
-constexpr int TW = 128;
-
-template <int D>
-struct WgradTile {
-    static constexpr int W = TW + 4 * D;  // staged positions of a
-    static constexpr int WS = W + 2;      // row stride of the a copies (even)
-    static constexpr size_t lds = (size_t)(CH * TW + 2 * CH * WS) * sizeof(__bf16);
-};
-
-__device__ __forceinline__ bf16x8 lds_read8_aligned4(const __bf16 *p) {
-    const uint32_t *q = reinterpret_cast<const uint32_t *>(p);
-    typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
-    u32x4 v = {q[0], q[1], q[2], q[3]};
-    return __builtin_bit_cast(bf16x8, v);
-}
-
-template <int D>
-__global__ void __launch_bounds__(256) k_hidden_wgrad(const __bf16 *__restrict__ dz, const __bf16 *__restrict__ a,
-                                                      float *__restrict__ part, float *__restrict__ partb, int B,
-                                                      int L) {
-    constexpr int W = WgradTile<D>::W, WS = WgradTile<D>::WS;
-    extern __shared__ unsigned char smem[];
-    __bf16 *dzT = reinterpret_cast<__bf16 *>(smem);  // [64][TW]
-    __bf16 *aT0 = dzT + CH * TW;                      // [64][WS]: aT0[c][p] = a[x0 - 2D + p, c]
-    __bf16 *aT1 = aT0 + CH * WS;                      // [64][WS]: aT1[c][p] = aT0[c][p + 1]
-    __shared__ float bred[4][CH];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m0 = 32 * (wave & 1), n0 = 32 * (wave >> 1);  // co block, ci block
-    const int lr = lane & 31, lk = 8 * (lane >> 5);
-    floatx16 acc[KT];
-#pragma unroll
-    for (int t = 0; t < KT; ++t) acc[t] = floatx16{};
-    float bsum = 0.0f;
-    const bf16x8 zero8 = {};
-    for (int b = blockIdx.x; b < B; b += gridDim.x) {
-        for (int x0 = 0; x0 < L; x0 += TW) {
-            __syncthreads();
-            for (int i = threadIdx.x; i < TW * (CH / 8); i += blockDim.x) {
-                const int p = i % TW, v = i / TW;
-                const bf16x8 val = *(const bf16x8 *)(dz + ((int64_t)b * L + x0 + p) * CH + 8 * v);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) dzT[(8 * v + j) * TW + p] = val[j];
-            }
-            for (int i = threadIdx.x; i < W * (CH / 8); i += blockDim.x) {
-                const int p = i % W, v = i / W;
-                const int pos = x0 - 2 * D + p;
-                const bf16x8 val =
-                    (pos >= 0 && pos < L) ? *(const bf16x8 *)(a + ((int64_t)b * L + pos) * CH + 8 * v) : zero8;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    aT0[(8 * v + j) * WS + p] = val[j];
-                    if (p > 0) aT1[(8 * v + j) * WS + p - 1] = val[j];
-                }
-            }
-            // bias gradient straight from global memory (rows of 64 channels, coalesced)
-#pragma unroll 4
-            for (int k = wave; k < TW; k += 4) bsum += to_f(dz[((int64_t)b * L + x0 + k) * CH + lane]);
-            __syncthreads();
-#pragma unroll 1
-            for (int ks = 0; ks < TW; ks += 16) {
-                const bf16x8 av = *(const bf16x8 *)(dzT + (m0 + lr) * TW + ks + lk);
-#pragma unroll
-                for (int tap = 0; tap < KT; ++tap) {
-                    const int o = ks + lk + tap * D;
-                    const bf16x8 bv = ((tap * D) & 1) ? lds_read8_aligned4(aT1 + (n0 + lr) * WS + o - 1)
-                                                      : lds_read8_aligned4(aT0 + (n0 + lr) * WS + o);
-                    acc[tap] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[tap], 0, 0, 0);
-                }
-            }
-        }
-    }
-    float *pg = part + (int64_t)blockIdx.x * KT * CH * CH;
-#pragma unroll
-    for (int tap = 0; tap < KT; ++tap)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int co = m0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            pg[(tap * CH + co) * CH + n0 + lr] = acc[tap][r];
-        }
-    // bias partial: per channel (lane), the four waves' sums in a fixed order
-    bred[wave][lane] = bsum;
-    __syncthreads();
-    if (wave == 0)
-        partb[(int64_t)blockIdx.x * CH + lane] = ((bred[0][lane] + bred[1][lane]) + bred[2][lane]) + bred[3][lane];
 }
 
 // ---------------------------------------------------------------------------
@@ -598,6 +318,10 @@ __global__ void __launch_bounds__(256) k_l4_fwd(const __bf16 *__restrict__ a3, c
 // ---------------------------------------------------------------------------
 constexpr int FC = 64, FR = 256, FMAXL = 4096;
 constexpr int FFP = FC + 8;  // feature buffer row: positions 64 c - 2 .. 64 c + 65
+// a segment of a sample starts its stream FLEAD positions early and ends it FLEAD
+// late: the reach of the four layers' taps, rounded up to a 32-row block
+constexpr int FLEAD = 96;
+static_assert(FLEAD >= 2 * (1 + 3 + 9 + 27) && FLEAD % 32 == 0, "the lead covers the taps");
 // lag of layer k >= lag of layer k - 1 + one chunk + the half-width 2 d_k of its
 // taps, rounded up to a multiple of 32 so that no 32-row block wraps its ring
 constexpr int FD2 = 96, FD3 = 192, FD4 = 320;
@@ -610,36 +334,49 @@ static_assert(FC >= 2 * 27, "the padding chunk between two samples covers the wi
 constexpr int FMAXS = 2;  // samples per workgroup (the sample of a stream position is one comparison)
 constexpr size_t FUSED_RINGS = (size_t)3 * FR * RS * sizeof(__bf16);  // then NS x 2 x (L + 4) floats of n, u
 
+template <bool KEEP, bool SEG>
 __global__ void __launch_bounds__(512) k_fwd_fused(const float *__restrict__ nu, const float *__restrict__ tau,
                                                    const __bf16 *__restrict__ W1, const float *__restrict__ b1,
                                                    const __bf16 *__restrict__ W2, const float *__restrict__ b2,
                                                    const __bf16 *__restrict__ W3, const float *__restrict__ b3,
                                                    const __bf16 *__restrict__ W4, const float *__restrict__ b4,
-                                                   float *__restrict__ out, int B, int L, int spw) {
+                                                   float *__restrict__ out, __bf16 *__restrict__ z1,
+                                                   __bf16 *__restrict__ z2, __bf16 *__restrict__ z3, int B, int L,
+                                                   int spw, int segs, int seglen) {
     extern __shared__ unsigned char smem[];
     __bf16 *r1 = reinterpret_cast<__bf16 *>(smem);  // a1 ring [FR][RS]
     __bf16 *r2 = r1 + FR * RS;                      // a2 ring
     __bf16 *r3 = r2 + FR * RS;                      // a3 ring
+    // the samples of this workgroup, or its segment: positions [x0, x0 + len) of one
+    // sample, the stream starting `lead` positions before
+    const int s0 = SEG ? (int)blockIdx.x / segs : (int)blockIdx.x * spw;
+    const int ns = SEG ? 1 : (B - s0 < spw ? B - s0 : spw);
+    const int x0 = SEG ? ((int)blockIdx.x % segs) * seglen : 0;
+    const int len = SEG && L - x0 >= seglen ? seglen : L - x0;
+    const int lead = x0 < FLEAD ? x0 : FLEAD, base = x0 - lead;
+    const int W = SEG ? (L - x0 - len < FLEAD ? L : x0 + len + FLEAD) - base : L;  // stream positions of a sample
     // per sample raw n then u, each with two cells of padding per side (n = 1, u = 0: features 0)
     float *nus = reinterpret_cast<float *>(smem + FUSED_RINGS);
-    const int LP = L + 4;
+    const int LP = W + 4;
     __shared__ unsigned short gt[GeluT32::N];       // GELU table
     __shared__ float feat[2 * 3 * FFP];             // features of the current and the next chunk
-    const int s0 = blockIdx.x * spw;
-    const int ns = B - s0 < spw ? B - s0 : spw;     // samples of this workgroup
-    const int SL = L + FC;                          // stream stride of a sample
+    const int SL = W + FC;                          // stream stride of a sample
     const int LT = ns * SL - FC;                    // stream length
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const bf16x8 zero8 = {};
     for (int i = threadIdx.x; i < 3 * FR * RS / 8; i += blockDim.x) reinterpret_cast<bf16x8 *>(smem)[i] = zero8;
-    for (int i = threadIdx.x; i < GeluT32::N; i += blockDim.x) gt[i] = GeluT32::entry(i);
+    GeluT32::fill(gt);
     for (int i = threadIdx.x; i < ns * 2 * LP; i += blockDim.x) {
         const int k = i / (2 * LP), r = i - k * 2 * LP;
-        const int ch = r >= LP, x = r - ch * LP - 2;
+        const int ch = r >= LP, x = base + r - ch * LP - 2;
         nus[i] = (x >= 0 && x < L) ? nu[(int64_t)(s0 + k) * 2 * L + (int64_t)ch * L + x] : (ch ? 0.0f : 1.0f);
     }
-    // stream position X < 2 SL: sample k = (X >= SL), local position X - k SL
-    auto inside = [&](int X) { return X >= 0 && X < LT && X - (X >= SL ? SL : 0) < L; };
+    // stream position X < 2 SL: sample k = (X >= SL), position base + X - k SL of it
+    auto inside = [&](int X) { return X >= 0 && X < LT && X - (X >= SL ? SL : 0) < W; };
+    // of the positions this workgroup writes
+    auto own = [&](int X) { return SEG ? X >= lead && X < lead + len : inside(X); };
+    // row of a stream position inside a sample in the kept activations
+    auto row_of = [&](int X) { return (int64_t)(s0 + (X >= SL)) * L + (base + X - (X >= SL ? SL : 0)); };
     // layers 1-3: this wave's block (positions 32 mb .., channels 32 nb ..)
     const bool upper = wave >= 4;  // layer 3 and layer 1
     const int mb = wave & 1, nb = (wave >> 1) & 1;
@@ -678,7 +415,7 @@ __global__ void __launch_bounds__(512) k_fwd_fused(const float *__restrict__ nu,
     const int d = upper ? 9 : 3, D = upper ? FD3 : FD2;
     const __bf16 *rin = upper ? r2 : r1;
     __bf16 *rout = upper ? r3 : r2;
-    const int niter = (LT + FD4 - 1) / FC + 1;
+    const int niter = ((SEG ? lead + len : LT) + FD4 - 1) / FC + 1;
     // Let the weight loads land before the loop: otherwise the compiler's wait
     // counts inside the loop stay conservative and every iteration's last matrix
     // operation waits for all vector-memory traffic in flight (the previous
@@ -690,7 +427,7 @@ __global__ void __launch_bounds__(512) k_fwd_fused(const float *__restrict__ nu,
     auto layer1 = [&](int c) {
         const int X = c * FC + 16 * pg1 + lc;  // this lane's position
         __bf16 *orow = r1 + (X & (FR - 1)) * RS + 32 * h1 + 4 * g1;
-        if (!inside(c * FC)) {
+        if (!inside(c * FC + (SEG ? 16 * pg1 : 0))) {
 #pragma unroll
             for (int q = 0; q < 2; ++q) *reinterpret_cast<uint2 *>(orow + 16 * q) = make_uint2(0u, 0u);
         } else {
@@ -711,6 +448,11 @@ __global__ void __launch_bounds__(512) k_fwd_fused(const float *__restrict__ nu,
                 zq[2 * q + 1] = pack_bf2(acc[2], acc[3]);
             }
             gelu_bf2_table<GeluT32>(zq, g, gt);
+            if (KEEP && (!SEG || own(c * FC + 16 * pg1))) {
+                __bf16 *zr = z1 + row_of(X) * CH + 32 * h1 + 4 * g1;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) *reinterpret_cast<uint2 *>(zr + 16 * q) = make_uint2(zq[2 * q], zq[2 * q + 1]);
+            }
 #pragma unroll
             for (int q = 0; q < 2; ++q) *reinterpret_cast<uint2 *>(orow + 16 * q) = make_uint2(g[2 * q], g[2 * q + 1]);
             if (__builtin_amdgcn_ballot_w64(gelu_bf2_outside<GeluT32>(zq) != 0u) != 0) {  // rare
@@ -755,6 +497,11 @@ __global__ void __launch_bounds__(512) k_fwd_fused(const float *__restrict__ nu,
 #pragma unroll
             for (int i = 0; i < 8; ++i) zq[i] = pack_bf2(acc[2 * i], acc[2 * i + 1]);
             gelu_bf2_table<GeluT32>(zq, g, gt);
+            if (KEEP && (!SEG || own(p0))) {
+                __bf16 *zr = (upper ? z3 : z2) + row_of(p0 + lr) * CH + nb * 32 + 4 * (lane >> 5);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) *reinterpret_cast<uint2 *>(zr + 8 * q) = make_uint2(zq[2 * q], zq[2 * q + 1]);
+            }
 #pragma unroll
             for (int q = 0; q < 4; ++q) *reinterpret_cast<uint2 *>(orow + 8 * q) = make_uint2(g[2 * q], g[2 * q + 1]);
             if (__builtin_amdgcn_ballot_w64(gelu_bf2_outside<GeluT32>(zq) != 0u) != 0) {  // rare
@@ -769,7 +516,7 @@ __global__ void __launch_bounds__(512) k_fwd_fused(const float *__restrict__ nu,
     // layer 4 (waves 0-3): 16 positions each, n' = n + 0.25 (b4 + y)
     auto layer4 = [&](int c) {
         const int p = c * FC - FD4 + 16 * wave;
-        if (inside(p)) {
+        if (own(p)) {
             floatx4 acc = {};
             bf16x8 av[2 * KT];  // all ten operands read before the first product
 #pragma unroll
@@ -783,7 +530,7 @@ __global__ void __launch_bounds__(512) k_fwd_fused(const float *__restrict__ nu,
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[kb], bw[kb], acc, 0, 0, 0);
             if (col < 2) {
                 const int k = p >= SL, xl = p - k * SL;
-                const int64_t o = (int64_t)(s0 + k) * 2 * L + (int64_t)col * L;
+                const int64_t o = (int64_t)(s0 + k) * 2 * L + (int64_t)col * L + base;
                 const float *nk = nus + k * 2 * LP + col * LP + 2;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -825,173 +572,6 @@ __global__ void __launch_bounds__(512) k_fwd_fused(const float *__restrict__ nu,
         features(c);
         __syncthreads();
     }
-}
-
-// Data gradient through layer 4 and the GELU of layer 3:
-//   da3[x, ci] = sum_{tap, c} dy[c, x - (tap-2) 27] W4[tap][c][ci],  dz3 = bf16(da3 GELU'(z3)),
-// with dy = 0.25 dout (the residual's scale).  8 threads per position, 8 channels each.
-__global__ void __launch_bounds__(256) k_l4_dgrad(const float *__restrict__ dout, const __bf16 *__restrict__ W4,
-                                                  const __bf16 *__restrict__ z3, __bf16 *__restrict__ dz3, int L) {
-    __shared__ float w[KT * 2 * CH];
-    for (int i = threadIdx.x; i < KT * 2 * CH; i += blockDim.x) w[i] = to_f(W4[i]);
-    __syncthreads();
-    const int b = blockIdx.y, x = blockIdx.x * 32 + (threadIdx.x >> 3), c8 = 8 * (threadIdx.x & 7);
-    if (x >= L) return;
-    float dyv[KT][2];
-#pragma unroll
-    for (int tap = 0; tap < KT; ++tap) {
-        const int pos = x - (tap - 2) * 27;
-        const bool ok = pos >= 0 && pos < L;
-        dyv[tap][0] = ok ? FS * dout[(int64_t)b * 2 * L + pos] : 0.0f;
-        dyv[tap][1] = ok ? FS * dout[(int64_t)b * 2 * L + L + pos] : 0.0f;
-    }
-    const int64_t row = ((int64_t)b * L + x) * CH + c8;
-    const bf16x8 zv = *(const bf16x8 *)(z3 + row);
-    bf16x8 dv;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int ci = c8 + j;
-        float acc = 0.0f;
-#pragma unroll
-        for (int tap = 0; tap < KT; ++tap) {
-            acc = __builtin_fmaf(dyv[tap][0], w[(tap * 2 + 0) * CH + ci], acc);
-            acc = __builtin_fmaf(dyv[tap][1], w[(tap * 2 + 1) * CH + ci], acc);
-        }
-        dv[j] = to_bf(acc * gelu_grad(to_f(zv[j])));
-    }
-    *(bf16x8 *)(dz3 + row) = dv;
-}
-
-// Fixed-order sum of 256 per-thread values (tree over an LDS array).
-__device__ __forceinline__ float block_sum256(float v, float *scratch) {
-    scratch[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) scratch[threadIdx.x] += scratch[threadIdx.x + s];
-        __syncthreads();
-    }
-    const float r = scratch[0];
-    __syncthreads();
-    return r;
-}
-
-// Weight gradient of layer 4: dW4[tap][c][ci] = sum_{b,x} dy[b, c, x] a3[b, x + (tap-2) 27, ci],
-// db4[c] = sum dy.  Workgroup g takes samples g, g + G, ...; thread (ci = t % 64,
-// group t / 64) walks a3 rows of chunks of 256 positions, with dy of the chunk
-// (and a 54-position halo) staged in LDS.  Partials part[g][642].
-constexpr int P4 = 256, H4 = 2 * 27;
-
-__global__ void __launch_bounds__(256) k_l4_wgrad(const float *__restrict__ dout, const __bf16 *__restrict__ a3,
-                                                  float *__restrict__ part, int B, int L) {
-    constexpr int NW = KT * 2 * CH;
-    __shared__ float dyl[2][P4 + 2 * H4];
-    __shared__ float red[4][NW];
-    __shared__ float tmp[256];
-    const int ci = threadIdx.x & 63, grp = threadIdx.x >> 6;
-    float acc[KT][2] = {};
-    float bacc0 = 0.0f, bacc1 = 0.0f;
-    for (int b = blockIdx.x; b < B; b += gridDim.x) {
-        const float *dyb = dout + (int64_t)b * 2 * L;
-        for (int p0 = 0; p0 < L; p0 += P4) {
-            __syncthreads();
-            for (int i = threadIdx.x; i < 2 * (P4 + 2 * H4); i += blockDim.x) {
-                const int c = i / (P4 + 2 * H4), k = i % (P4 + 2 * H4);
-                const int x = p0 - H4 + k;
-                dyl[c][k] = (x >= 0 && x < L) ? FS * dyb[c * L + x] : 0.0f;
-            }
-            __syncthreads();
-            if (p0 + threadIdx.x < L) {
-                bacc0 += dyl[0][H4 + threadIdx.x];
-                bacc1 += dyl[1][H4 + threadIdx.x];
-            }
-            const int kend = min(P4, L - p0);
-#pragma unroll 4
-            for (int k = grp; k < kend; k += 4) {
-                const float a = to_f(a3[((int64_t)b * L + p0 + k) * CH + ci]);
-#pragma unroll
-                for (int tap = 0; tap < KT; ++tap) {
-                    const int idx = k + H4 - (tap - 2) * 27;
-                    acc[tap][0] = __builtin_fmaf(dyl[0][idx], a, acc[tap][0]);
-                    acc[tap][1] = __builtin_fmaf(dyl[1][idx], a, acc[tap][1]);
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int tap = 0; tap < KT; ++tap) {
-        red[grp][(tap * 2 + 0) * CH + ci] = acc[tap][0];
-        red[grp][(tap * 2 + 1) * CH + ci] = acc[tap][1];
-    }
-    __syncthreads();
-    float *pg = part + (int64_t)blockIdx.x * (NW + 2);
-    for (int o = threadIdx.x; o < NW; o += blockDim.x) pg[o] = ((red[0][o] + red[1][o]) + red[2][o]) + red[3][o];
-    const float s0 = block_sum256(bacc0, tmp);
-    const float s1 = block_sum256(bacc1, tmp);
-    if (threadIdx.x == 0) {
-        pg[NW] = s0;
-        pg[NW + 1] = s1;
-    }
-}
-
-// Weight gradient of layer 1: dW1[tap][co][ci] = sum_{b,x} dz1[b, x, co] f[b, ci, x + tap - 2],
-// db1[co] = sum dz1.  Thread (co = t % 64, group t / 64) walks the positions of
-// chunks of 256 with the chunk's features (and a 2-position halo) in LDS.
-// Partials part[g][5*64*3 + 64].
-constexpr int P1W = 256;
-
-__global__ void __launch_bounds__(256) k_l1_wgrad(const __bf16 *__restrict__ dz1, const float *__restrict__ nu,
-                                                  const float *__restrict__ tau, float *__restrict__ part, int B,
-                                                  int L) {
-    constexpr int NW = KT * CH * 3;
-    __shared__ float red[4][NW + CH];
-    __shared__ float fs[3][P1W + 4];
-    const int co = threadIdx.x & 63, grp = threadIdx.x >> 6;
-    float acc[KT][3] = {};
-    float bacc = 0.0f;
-    for (int b = blockIdx.x; b < B; b += gridDim.x) {
-        for (int p0 = 0; p0 < L; p0 += P1W) {
-            __syncthreads();
-            for (int i = threadIdx.x; i < 3 * (P1W + 4); i += blockDim.x) {
-                const int c = i / (P1W + 4), k = i % (P1W + 4);
-                fs[c][k] = feature(nu, tau, b, L, c, p0 - 2 + k);
-            }
-            __syncthreads();
-            const int kend = min(P1W, L - p0);
-#pragma unroll 4
-            for (int k = grp; k < kend; k += 4) {
-                const float g = to_f(dz1[((int64_t)b * L + p0 + k) * CH + co]);
-                bacc += g;
-#pragma unroll
-                for (int t = 0; t < KT; ++t)
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) acc[t][c] = __builtin_fmaf(g, fs[c][k + t], acc[t][c]);
-            }
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < KT; ++t)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) red[grp][(t * CH + co) * 3 + c] = acc[t][c];
-    red[grp][NW + co] = bacc;
-    __syncthreads();
-    for (int o = threadIdx.x; o < NW + CH; o += blockDim.x)
-        part[(int64_t)blockIdx.x * (NW + CH) + o] = ((red[0][o] + red[1][o]) + red[2][o]) + red[3][o];
-}
-
-// dst[i] = sum over g of part[g][i] in a fixed order: four interleaved partial
-// sums (g = j mod 4), then ((s0 + s1) + s2) + s3.  64 outputs per workgroup.
-__global__ void __launch_bounds__(256) k_reduce(const float *__restrict__ part, int G, int n, float *__restrict__ dst) {
-    __shared__ float sums[4][64];
-    const int t = threadIdx.x & 63, j = threadIdx.x >> 6;
-    const int i = blockIdx.x * 64 + t;
-    float a = 0.0f;
-    if (i < n) {
-#pragma unroll 8
-        for (int g = j; g < G; g += 4) a += part[(int64_t)g * n + i];
-    }
-    sums[j][t] = a;
-    __syncthreads();
-    if (j == 0 && i < n) dst[i] = ((sums[0][t] + sums[1][t]) + sums[2][t]) + sums[3][t];
 }
 
 // ---------------------------------------------------------------------------
@@ -1131,80 +711,26 @@ hipError_t l1_fwd(const float *nu, const float *tau, const __bf16 *W1, const flo
     return hipGetLastError();
 }
 
-// Kernels with more than 64 KB of dynamic LDS need their limit raised, on each
-// device they run on: once per device and kernel, under a lock.
-constexpr int kMaxDevices = 64;
-struct LdsLimit {
-    std::mutex m;
-    bool done[kMaxDevices] = {};
-    hipError_t raise(const void *fn, int bytes) {
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e != hipSuccess) return e;
-        if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-        std::lock_guard<std::mutex> lock(m);
-        if (done[dev]) return hipSuccess;
-        e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-        if (e == hipSuccess) done[dev] = true;
-        return e;
-    }
-};
+size_t hidden_lds(int d) { return (size_t)(KT * CH + TM + 4 * d) * RS * sizeof(__bf16); }
 
-size_t hidden_lds(int d, bool dgrad) {
-    size_t tile = (size_t)(TM + 4 * d) * RS * sizeof(__bf16);
-    if (dgrad && tile < (size_t)TM * RSF * sizeof(float)) tile = (size_t)TM * RSF * sizeof(float);
-    return (size_t)KT * CH * RS * sizeof(__bf16) + tile;
-}
-
-hipError_t hidden(bool dgrad, const __bf16 *in, const __bf16 *Wop, const float *bias, const __bf16 *zprev,
-                  __bf16 *out_z, __bf16 *out_a, int B, int L, int d, hipStream_t s) {
-    if (L % TM) return hipErrorInvalidValue;
-    static LdsLimit fwd_limit, dgrad_limit;
-    hipError_t attr = dgrad ? dgrad_limit.raise((const void *)k_hidden<true>, (int)hidden_lds(9, true))
-                            : fwd_limit.raise((const void *)k_hidden<false>, (int)hidden_lds(9, false));
+hipError_t hidden(const __bf16 *in, const __bf16 *Wop, const float *bias, __bf16 *out_z, __bf16 *out_a, int B, int L,
+                  int d, hipStream_t s) {
+    if (L % TM || (d != 3 && d != 9)) return hipErrorInvalidValue;
+    static LdsLimit limit;
+    const hipError_t attr = limit.raise((const void *)k_hidden, (int)hidden_lds(9));
     if (attr != hipSuccess) return attr;
-    if (d != 3 && d != 9) return hipErrorInvalidValue;
     const int ntiles = B * (L / TM);
     const int grid = ntiles < 512 ? ntiles : 512;  // two workgroups per CU (about 70 KB of LDS each)
-    if (dgrad)
-        hipLaunchKernelGGL(k_hidden<true>, dim3(grid), dim3(256), hidden_lds(d, true), s, in, Wop, bias, zprev, out_z, out_a,
-                           B, L, d);
-    else
-        hipLaunchKernelGGL(k_hidden<false>, dim3(grid), dim3(256), hidden_lds(d, false), s, in, Wop, bias, zprev, out_z,
-                           out_a, B, L, d);
-    return hipGetLastError();
-}
-
-hipError_t hidden_wgrad(const __bf16 *dz, const __bf16 *a, float *part, float *partb, int G, int B, int L, int d,
-                        hipStream_t s) {
-    if (d == 3)
-        hipLaunchKernelGGL(k_hidden_wgrad<3>, dim3(G), dim3(256), WgradTile<3>::lds, s, dz, a, part, partb, B, L);
-    else if (d == 9)
-        hipLaunchKernelGGL(k_hidden_wgrad<9>, dim3(G), dim3(256), WgradTile<9>::lds, s, dz, a, part, partb, B, L);
-    else
-        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_hidden, dim3(grid), dim3(256), hidden_lds(d), s, in, Wop, bias, out_z, out_a, B, L, d);
     return hipGetLastError();
 }
 
 int fused_max_length() { return FMAXL; }
 
-// Compute units of the current device (cached per device).
-static int device_cus() {
-    static std::mutex m;
-    static int cus[kMaxDevices] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
-    std::lock_guard<std::mutex> lock(m);
-    if (cus[dev] == 0 && hipDeviceGetAttribute(&cus[dev], hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        cus[dev] = 0;
-    return cus[dev];
-}
-
 hipError_t fwd_fused(const float *nu, const float *tau, const __bf16 *W1, const float *b1, const __bf16 *W2,
                      const float *b2, const __bf16 *W3, const float *b3, const __bf16 *W4, const float *b4, float *out,
-                     int B, int L, hipStream_t s) {
+                     __bf16 *z1, __bf16 *z2, __bf16 *z3, int B, int L, hipStream_t s) {
     if (B < 1 || L < FC || L % FC || L > FMAXL) return hipErrorInvalidValue;
-    static LdsLimit limit;
     constexpr size_t kMaxStage = (size_t)2 * (FMAXL + 4) > (size_t)FMAXS * 2 * (FMAXL / FMAXS + 4)
                                      ? (size_t)2 * (FMAXL + 4)
                                      : (size_t)FMAXS * 2 * (FMAXL / FMAXS + 4);
@@ -1212,44 +738,44 @@ hipError_t fwd_fused(const float *nu, const float *tau, const __bf16 *W1, const 
     static_assert(FUSED_RINGS + kMaxStage * sizeof(float) + GeluT32::N * sizeof(unsigned short) +
                           2 * 3 * FFP * sizeof(float) <= 160 * 1024,
                   "LDS of the largest staging");
-    const hipError_t attr = limit.raise((const void *)k_fwd_fused, (int)(FUSED_RINGS + kMaxStage * sizeof(float)));
-    if (attr != hipSuccess) return attr;
     // two samples per workgroup once there are more samples than compute units
     // (one workgroup fits a CU): the padding chunk between them replaces the
     // pipeline's fill and drain, and no second wave of workgroups is needed
     const int cus = device_cus();
     const int spw = (cus > 0 && B > cus && L * FMAXS <= FMAXL) ? FMAXS : 1;
-    const int grid = (B + spw - 1) / spw;
-    const size_t lds = FUSED_RINGS + (size_t)spw * 2 * (L + 4) * sizeof(float);
-    hipLaunchKernelGGL(k_fwd_fused, dim3(grid), dim3(512), lds, s, nu, tau, W1, b1, W2, b2, W3, b3, W4, b4, out, B, L,
-                       spw);
+    // With fewer samples than compute units a sample is cut into segments of whole
+    // chunks, one workgroup each: a workgroup takes len / 64 + 5 iterations for len
+    // positions and 1.5 more for a segment's lead, which the cut has to repay.
+    // Whole samples against segments, us per call: 1 x 384 23.6 -> 19.3, 1 x 1024
+    // 41.2 -> 19.7, 1 x 4096 126 -> 20.0, 64 x 1024 42.8 -> 27.4, 40 x 4096 128 -> 40.5
+    // (layer by layer with the activations kept: 26.6, 27.8, 29.2, 47.2, 69.0).
+    int segs = 1, seglen = L;
+    if (cus > 0 && B < cus) {
+        const int want = cus / B < L / FC ? cus / B : L / FC;
+        const int sl = (L / FC + want - 1) / want * FC;
+        if (sl + FLEAD < L) {
+            seglen = sl;
+            segs = (L + sl - 1) / sl;
+        }
+    }
+    const int grid = segs > 1 ? B * segs : (B + spw - 1) / spw;
+    const int window = segs > 1 && seglen + 2 * FLEAD < L ? seglen + 2 * FLEAD : L;
+    const size_t lds = FUSED_RINGS + (size_t)spw * 2 * (window + 4) * sizeof(float);
+    using Kernel = decltype(&k_fwd_fused<false, false>);
+    static constexpr Kernel kernels[4] = {k_fwd_fused<false, false>, k_fwd_fused<true, false>, k_fwd_fused<false, true>,
+                                          k_fwd_fused<true, true>};
+    static LdsLimit limits[4];
+    const int v = (z1 ? 1 : 0) + (segs > 1 ? 2 : 0);
+    const hipError_t attr = limits[v].raise((const void *)kernels[v], (int)(FUSED_RINGS + kMaxStage * sizeof(float)));
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(kernels[v], dim3(grid), dim3(512), lds, s, nu, tau, W1, b1, W2, b2, W3, b3, W4, b4, out, z1, z2, z3,
+                       B, L, spw, segs, seglen);
     return hipGetLastError();
 }
 
 hipError_t l4_fwd(const __bf16 *a3, const __bf16 *W4, const float *b4, const float *nu, float *out, int B, int L,
                   hipStream_t s) {
     hipLaunchKernelGGL(k_l4_fwd, dim3((L + P4F - 1) / P4F, B), dim3(256), 0, s, a3, W4, b4, nu, out, L);
-    return hipGetLastError();
-}
-
-hipError_t l4_dgrad(const float *dout, const __bf16 *W4, const __bf16 *z3, __bf16 *dz3, int B, int L, hipStream_t s) {
-    hipLaunchKernelGGL(k_l4_dgrad, dim3((L + 31) / 32, B), dim3(256), 0, s, dout, W4, z3, dz3, L);
-    return hipGetLastError();
-}
-
-hipError_t l4_wgrad(const float *dout, const __bf16 *a3, float *part, int G, int B, int L, hipStream_t s) {
-    hipLaunchKernelGGL(k_l4_wgrad, dim3(G), dim3(256), 0, s, dout, a3, part, B, L);
-    return hipGetLastError();
-}
-
-hipError_t l1_wgrad(const __bf16 *dz1, const float *nu, const float *tau, float *part, int G, int B, int L,
-                    hipStream_t s) {
-    hipLaunchKernelGGL(k_l1_wgrad, dim3(G), dim3(256), 0, s, dz1, nu, tau, part, B, L);
-    return hipGetLastError();
-}
-
-hipError_t reduce(const float *part, int G, int n, float *dst, hipStream_t s) {
-    hipLaunchKernelGGL(k_reduce, dim3((n + 63) / 64), dim3(256), 0, s, part, G, n, dst);
     return hipGetLastError();
 }
 

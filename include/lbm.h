@@ -171,7 +171,7 @@ lbm_status lbm_init(const lbm_config *cfg, void *workspace, size_t bytes, void *
                     const double *n0_dev, const double *u0_dev, lbm_ctx *out);
 
 /* Advance nsteps lattice BGK steps (lattice BGK equation: stream, moments,
- * equilibrium, relaxation), fused into one kernel per step, or per 2 to 6 steps
+ * equilibrium, relaxation), fused into one kernel per step, or per several steps
  * (lbm_workspace_bytes; the same results bit for bit).  An even nsteps leaves
  * the state in the lattice it was in.  Asynchronous. */
 lbm_status lbm_step(lbm_ctx ctx, int64_t nsteps);

@@ -146,6 +146,7 @@ struct lbm_ctx_s {
     hipStream_t cap = nullptr;  // private stream for graph capture
     bool multi = false;   // calls of several steps run as passes between the two lattices
     MultiPlan plan{};
+    TilePlan tile{};      // small boxes (h > 0): tiles in LDS instead
     hipGraphExec_t graph[2] = {nullptr, nullptr};  // by starting parity / lattice index
 };
 
@@ -166,7 +167,7 @@ hipError_t one_step(lbm_ctx_s *c, hipStream_t s) {
     return e;
 }
 
-// n steps: passes of several steps where the box takes them, else one by one.
+// n steps: launches of several steps where the box takes them, else one by one.
 // Passes start and end in natural layout, so an AA run takes an odd step before
 // and after on its own; after n steps the state is in the lattice that n single
 // steps leave it in (a caller may capture the call and replay it).
@@ -180,6 +181,20 @@ hipError_t enqueue_steps(lbm_ctx_s *c, int64_t n, hipStream_t s) {
         }
         int64_t m = aa ? n & ~int64_t(1) : n;
         n -= m;
+        if (c->tile.h > 0) {
+            // equal launches, as many as keep the parity of the launches that of the steps
+            int64_t k = (m + c->tile.h - 1) / c->tile.h;
+            if ((k ^ (aa ? 0 : m)) & 1) ++k;
+            for (; e == hipSuccess && m > 0; --k) {
+                const int h = (int)((m + k - 1) / k);
+                e = launch_tile(c->fp64, c->tile, h, c->lat[c->cur], c->lat[1 - c->cur], c->lm, c->box, c->model,
+                                c->cfg.tau, c->rho_ref, c->F, s);
+                if (e != hipSuccess) return e;
+                c->cur = 1 - c->cur;
+                c->steps += h;
+                m -= h;
+            }
+        }
         for (int odd = aa ? 0 : (int)(m & 1); m > 0 && e == hipSuccess; odd ^= 1) {
             const int H = multi_depth(c->plan, m, odd);
             if (H < 2) {
@@ -310,7 +325,10 @@ lbm_status lbm_init(const lbm_config *cfg, void *workspace, size_t bytes, void *
         int dev = 0, cus = 0;
         e = hipGetDevice(&dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        c->plan = multi_plan(cfg->nx, cfg->ny, c->fp64, lay.porous || c->box.bbx || c->box.bby, lay.nlat == 2, cus);
+const bool links = lay.porous || c->box.bbx || c->box.bby;
+        c->plan = multi_plan(cfg->nx, cfg->ny, c->fp64, links, lay.nlat == 2, cus);
+        c->tile = tile_plan(cfg->nx, cfg->ny, c->box.bbx, c->box.bby, lay.porous, c->fp64, cus);
+        if (c->tile.time >= c->plan.time) c->tile.h = 0;
     }
     if (e == hipSuccess && c->lm) e = hipMemsetAsync(c->lm, 0, (size_t)lay.cells * sizeof(uint32_t), c->stream);  // no solids yet
     if (e == hipSuccess)

@@ -1,5 +1,5 @@
-// Several steps of a d2v9 box per pass (lbm_multi.hip): which boxes, how deep,
-// and the launch.
+// Several steps of a d2v9 box per pass: in registers (lbm_multi.hip), which boxes,
+// how deep and the launch; small boxes in LDS (lbm_tile.hip).
 #pragma once
 
 #include "lbm_internal.h"
@@ -10,6 +10,7 @@ constexpr int kMultiTail = 24;  // the last steps of a call, planned together
 
 struct MultiPlan {
     int best = 0;     // steps per pass
+    double time = 0;  // estimated microseconds per step
     int ly[8] = {};   // rows per segment, by depth
     // the next launch (1: a single step, 0: none fits) of n steps that are to take
     // an even (0) or odd (1) number of launches
@@ -25,5 +26,19 @@ int multi_depth(const MultiPlan &p, int64_t n, int odd);
 // H steps from src into dst (another lattice), both in natural layout.
 hipError_t launch_multi(int fp64, int H, const void *src, void *dst, const uint32_t *lm, const Box &b, const Model &m,
                         double tau, double rho_ref, const double *F, int ly, hipStream_t s);
+
+
+// Small boxes: tiles in LDS (lbm_tile.hip).
+constexpr int kTileSteps = 4096;  // most steps of one launch
+
+struct TilePlan {
+    int sx = 0, sy = 0;  // tile
+    int h = 0;           // steps per launch
+    double time = 0;     // estimated microseconds per step
+};
+TilePlan tile_plan(int nx, int ny, bool bbx, bool bby, bool porous, int fp64, int cus);
+// h <= p.h steps from src into dst, both in natural layout.
+hipError_t launch_tile(int fp64, const TilePlan &p, int h, const void *src, void *dst, const uint32_t *lm,
+                       const Box &b, const Model &m, double tau, double rho_ref, const double *F, hipStream_t s);
 
 }  // namespace lbm

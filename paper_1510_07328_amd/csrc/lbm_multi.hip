@@ -360,6 +360,7 @@ MultiPlan multi_plan(int nx, int ny, int fp64, bool links, bool single, int cus)
             p.best = H;
         }
     }
+    p.time = best;
     // The last steps: the cheapest launches that sum to n, by their count's parity
     // (the state has to end in the lattice that n single steps leave it in).
     pass[1] = 2.0 * bytes / 6e6 + 3.0;

@@ -1,11 +1,10 @@
-"""Calls of several steps on d2v9 boxes run as passes of several steps between two
-lattices (lbm_multi.hip).  Every cell update is the same arithmetic in the same
-order as in the single-step kernels, so one call of n steps must equal n calls of
-one step bit for bit: over strips and segments that end inside a box, boxes
-smaller than a strip, walls, solid cells with a force, both schemes and
-precisions, and the numbers of steps around each depth."""
-import ctypes as C
-
+"""Calls of several steps on d2v9 boxes run as launches of several steps between two
+lattices: small boxes as tiles in LDS (lbm_tile.hip), larger ones in registers
+(lbm_multi.hip).  Every cell update is the same arithmetic in the same order as in
+the single-step kernels, so one call of n steps must equal n calls of one step bit
+for bit: over tiles, strips and segments that end inside a box, boxes smaller than
+one, walls, solid cells with a force, both schemes and precisions, and the numbers
+of steps around each depth."""
 import numpy as np
 import pytest
 import torch
@@ -26,7 +25,7 @@ def make(shape, bc=(0, 0, 0), porous=False, **kw):
 
 
 def solid_of(shape):
-    return inputs.porous_obstacles(shape, max(1, shape[0] * shape[1] // 300), 2.0, seed=3)
+    return inputs.porous_obstacles(shape, min(60, max(1, shape[0] * shape[1] // 300)), 2.0, seed=3)
 
 
 def run(cfg, n0, u0, calls, solid=None):
@@ -47,9 +46,11 @@ def run(cfg, n0, u0, calls, solid=None):
 @pytest.mark.parametrize("scheme", [PUSH, AA])
 @pytest.mark.parametrize("precision", [lbm.LBM_FP32_DEV, lbm.LBM_FP64])
 @pytest.mark.parametrize("shape,bc,porous,order", [
-    ((200, 90), (0, 0, 0), False, 2),    # several strips, the last one cut
-    ((61, 50), (0, 0, 0), False, 3),     # one strip and a part of one
-    ((5, 3), (0, 0, 0), False, 2),       # a strip wraps round the box many times
+    ((200, 90), (0, 0, 0), False, 2),    # tiles cut in both axes, the last ones short
+    ((61, 50), (0, 0, 0), False, 3),
+    ((700, 7), (0, 0, 0), False, 2),     # one axis whole
+    ((300, 4), (1, 0, 0), False, 2),
+    ((5, 3), (0, 0, 0), False, 2),       # the whole box in one window
     ((1, 64), (0, 0, 0), False, 2),
     ((131, 1), (1, 0, 0), False, 2),
     ((131, 40), (1, 0, 0), False, 2),    # walls in x, in y, in both
@@ -57,6 +58,7 @@ def run(cfg, n0, u0, calls, solid=None):
     ((58, 9), (1, 1, 0), False, 3),
     ((150, 70), (0, 0, 0), True, 2),     # solid cells and a force, without and with walls
     ((77, 41), (1, 1, 0), True, 3),
+    ((23, 11), (1, 1, 0), True, 2),
 ])
 def test_one_call_of_n_steps_equals_n_calls(gpu, shape, bc, porous, order, precision, scheme):
     cfg, n0, u0 = make(shape, bc, porous, order=order, precision=precision, scheme=scheme)
@@ -70,12 +72,24 @@ def test_one_call_of_n_steps_equals_n_calls(gpu, shape, bc, porous, order, preci
 
 
 @pytest.mark.parametrize("scheme", [PUSH, AA])
-def test_large_boxes_take_deep_passes(gpu, scheme):
-    """A box whose plan is the deepest pass (several wavefronts per SIMD), ragged against strips and segments."""
-    cfg, n0, u0 = make((2111, 1537), order=2, scheme=scheme)
-    one, _ = run(cfg, n0, u0, [1] * 26)
-    many, _ = run(cfg, n0, u0, [26])
-    assert np.array_equal(one, many)
+@pytest.mark.parametrize("shape,bc,porous,order,precision", [
+    ((2111, 1537), (0, 0, 0), False, 2, lbm.LBM_FP32_DEV),   # the deepest pass
+    ((1601, 1203), (0, 0, 0), False, 2, lbm.LBM_FP64),
+    ((1030, 777), (1, 0, 0), False, 2, lbm.LBM_FP32_DEV),    # strips at walls in x
+    ((1030, 777), (1, 1, 0), False, 3, lbm.LBM_FP64),
+    ((901, 811), (0, 1, 0), False, 2, lbm.LBM_FP32_DEV),
+    ((1000, 700), (0, 0, 0), True, 2, lbm.LBM_FP32_DEV),
+    ((1000, 700), (1, 1, 0), True, 3, lbm.LBM_FP64),
+    ((57, 20011), (0, 0, 0), False, 2, lbm.LBM_FP32_DEV),    # one strip and a part of one
+])
+def test_large_boxes(gpu, shape, bc, porous, order, precision, scheme):
+    """Boxes beyond the LDS tiles: the register pipeline at the depths and segments of its plan."""
+    cfg, n0, u0 = make(shape, bc, porous, order=order, precision=precision, scheme=scheme)
+    solid = solid_of(shape) if porous else None
+    for n in (5, 10, 26):
+        one, _ = run(cfg, n0, u0, [1] * n, solid)
+        many, _ = run(cfg, n0, u0, [n], solid)
+        assert np.array_equal(one, many), (n, int((one != many).sum()))
 
 
 def test_aa_runs_in_a_workspace_of_one_lattice(gpu):

@@ -22,8 +22,8 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(BUILD, "liblbm.so")
 
-SOURCES = ["coeffs.cpp", "lbm_kernels.hip", "lbm_multi.hip", "lbm_tile.hip", "lbm_capi.hip", "lbm_batch.hip",
-           "lbm_batch_capi.hip", "srg_kernels.hip", "srg_backward.hip", "srg_capi.hip"]
+SOURCES = ["coeffs.cpp", "lbm_kernels.hip", "lbm_multi.hip", "lbm_multi3.hip", "lbm_tile.hip", "lbm_capi.hip",
+           "lbm_batch.hip", "lbm_batch_capi.hip", "srg_kernels.hip", "srg_backward.hip", "srg_capi.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",

@@ -112,7 +112,8 @@ lbm_status check_config(const lbm_config *cfg, Model *m, Layout *lay) {
     lay->stage_rows = (int)srows;
     const size_t stage = align_up((size_t)srows * row_bytes);
     lay->min_total = lay->total = lay->stage_off + stage;
-    lay->multi = multi_eligible(cfg->lattice, m->local != 0, cfg->nx, cfg->ny, lay->plane, lay->elt);
+    const bool links = lay->porous || cfg->bc[0] || cfg->bc[1] || cfg->bc[2];
+    lay->multi = multi_eligible(cfg->lattice, m->local != 0, links, lay->plane, lay->elt);
     // AA: the second lattice of the passes, which between calls is free for the staging
     if (lay->multi && lay->nlat == 1)
         lay->total = lay->stage_off + (lay->lattice_bytes > stage ? lay->lattice_bytes : stage);
@@ -147,6 +148,7 @@ struct lbm_ctx_s {
     bool multi = false;   // calls of several steps run as passes between the two lattices
     MultiPlan plan{};
     TilePlan tile{};      // small boxes (h > 0): tiles in LDS instead
+    int lz = 0;           // d3v19: planes per segment of a pass of two steps (0: single steps)
     hipGraphExec_t graph[2] = {nullptr, nullptr};  // by starting parity / lattice index
 };
 
@@ -195,7 +197,16 @@ hipError_t enqueue_steps(lbm_ctx_s *c, int64_t n, hipStream_t s) {
                 m -= h;
             }
         }
-        for (int odd = aa ? 0 : (int)(m & 1); m > 0 && e == hipSuccess; odd ^= 1) {
+        for (; c->lz > 0 && m >= 4 && e == hipSuccess; m -= 4) {  // in pairs: back to the same lattice
+            for (int k = 0; k < 2 && e == hipSuccess; ++k) {
+                e = launch_multi3(c->fp64, c->lat[c->cur], c->lat[1 - c->cur], c->box, c->model, c->cfg.tau, c->rho_ref,
+                                  c->lz, s);
+                if (e != hipSuccess) return e;
+                c->cur = 1 - c->cur;
+                c->steps += 2;
+            }
+        }
+        for (int odd = aa ? 0 : (int)(m & 1); c->model.D == 2 && m > 0 && e == hipSuccess; odd ^= 1) {
             const int H = multi_depth(c->plan, m, odd);
             if (H < 2) {
                 if (H == 0) break;
@@ -325,10 +336,14 @@ lbm_status lbm_init(const lbm_config *cfg, void *workspace, size_t bytes, void *
         int dev = 0, cus = 0;
         e = hipGetDevice(&dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-const bool links = lay.porous || c->box.bbx || c->box.bby;
-        c->plan = multi_plan(cfg->nx, cfg->ny, c->fp64, links, lay.nlat == 2, cus);
-        c->tile = tile_plan(cfg->nx, cfg->ny, c->box.bbx, c->box.bby, lay.porous, c->fp64, cus);
-        if (c->tile.time >= c->plan.time) c->tile.h = 0;
+        const bool links = lay.porous || c->box.bbx || c->box.bby;
+        if (m.D == 3) {
+            c->lz = multi3_plan(cfg->nx, cfg->ny, cfg->nz, c->fp64, cus);
+        } else {
+            c->plan = multi_plan(cfg->nx, cfg->ny, c->fp64, links, lay.nlat == 2, cus);
+            c->tile = tile_plan(cfg->nx, cfg->ny, c->box.bbx, c->box.bby, lay.porous, c->fp64, cus);
+            if (c->tile.time >= c->plan.time) c->tile.h = 0;
+        }
     }
     if (e == hipSuccess && c->lm) e = hipMemsetAsync(c->lm, 0, (size_t)lay.cells * sizeof(uint32_t), c->stream);  // no solids yet
     if (e == hipSuccess)

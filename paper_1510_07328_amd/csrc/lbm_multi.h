@@ -2,9 +2,30 @@
 // how deep and the launch; small boxes in LDS (lbm_tile.hip).
 #pragma once
 
+#include <mutex>
+
 #include "lbm_internal.h"
 
 namespace lbm {
+
+// Kernels with more than 64 KB of dynamic LDS need their limit raised, on each
+// device they run on: once per device and kernel, under a lock.
+struct LdsLimit {
+    static constexpr int kMaxDevices = 64;
+    std::mutex m;
+    bool done[kMaxDevices] = {};
+    hipError_t raise(const void *fn, int bytes) {
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+        std::lock_guard<std::mutex> lock(m);
+        if (done[dev]) return hipSuccess;
+        e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        if (e == hipSuccess) done[dev] = true;
+        return e;
+    }
+};
 
 constexpr int kMultiTail = 24;  // the last steps of a call, planned together
 
@@ -17,8 +38,8 @@ struct MultiPlan {
     signed char next[kMultiTail + 1][2] = {};
 };
 
-// d2v9, one weight for all cells, a lattice below 4 GiB
-bool multi_eligible(int lattice, bool local, int nx, int ny, int64_t plane, size_t elt);
+// d2v9, or d3v19 without walls, solids or a force; one weight for all cells, a lattice below 4 GiB
+bool multi_eligible(int lattice, bool local, bool links, int64_t plane, size_t elt);
 // links: walls or solid cells; single: a single step may stand between passes (push; an AA step changes the layout)
 MultiPlan multi_plan(int nx, int ny, int fp64, bool links, bool single, int cus);
 // The next launch of n > 0 steps that are to take an even or odd number of launches.
@@ -27,6 +48,12 @@ int multi_depth(const MultiPlan &p, int64_t n, int odd);
 hipError_t launch_multi(int fp64, int H, const void *src, void *dst, const uint32_t *lm, const Box &b, const Model &m,
                         double tau, double rho_ref, const double *F, int ly, hipStream_t s);
 
+
+// Two steps of a periodic d3v19 box per pass (lbm_multi3.hip), segments of lz
+// planes (multi3_plan: 0 where single steps are faster).
+int multi3_plan(int nx, int ny, int nz, int fp64, int cus);
+hipError_t launch_multi3(int fp64, const void *src, void *dst, const Box &b, const Model &m, double tau,
+                         double rho_ref, int lz, hipStream_t s);
 
 // Small boxes: tiles in LDS (lbm_tile.hip).
 constexpr int kTileSteps = 4096;  // most steps of one launch

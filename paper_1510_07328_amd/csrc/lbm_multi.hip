@@ -303,10 +303,11 @@ constexpr int kDepths[] = {2, 3, 4, 6};
 
 }  // namespace
 
-bool multi_eligible(int lattice, bool local, int nx, int ny, int64_t plane, size_t elt) {
+bool multi_eligible(int lattice, bool local, bool links, int64_t plane, size_t elt) {
     // 32-bit byte offsets from the lattice base, as in the single-step kernels
-    return lattice == LBM_D2V9 && !local && nx >= 1 && ny >= 1 &&
-           (uint64_t)Q * (uint64_t)plane * elt < (uint64_t(1) << 32);
+    const int q = lattice == LBM_D2V9 ? D2Q9::Q : D3Q19::Q;
+    return !local && (lattice == LBM_D2V9 || (lattice == LBM_D3V19 && !links)) &&
+           (uint64_t)q * (uint64_t)plane * elt < (uint64_t(1) << 32);
 }
 
 int multi_depth(const MultiPlan &p, int64_t n, int odd) {

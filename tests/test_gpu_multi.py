@@ -92,6 +92,26 @@ def test_large_boxes(gpu, shape, bc, porous, order, precision, scheme):
         assert np.array_equal(one, many), (n, int((one != many).sum()))
 
 
+@pytest.mark.parametrize("scheme", [PUSH, AA])
+@pytest.mark.parametrize("shape,order,precision", [
+    ((64, 64, 64), 2, lbm.LBM_FP32_DEV),     # strips of 62 columns and 14 rows, the last ones short
+    ((62, 42, 100), 2, lbm.LBM_FP32_DEV),    # exact strips and groups
+    ((130, 45, 61), 3, lbm.LBM_FP32_DEV),
+    ((64, 31, 128), 2, lbm.LBM_FP64),        # groups of 6 rows
+    ((33, 300, 21), 3, lbm.LBM_FP64),
+])
+def test_periodic_d3v19_boxes(gpu, shape, order, precision, scheme):
+    """Two steps per pass in pairs of passes, and the steps left over."""
+    nx, ny, nz = shape
+    cfg = lbm.make_config("d3v19", shape=shape, order=order, tau=0.7, precision=precision, scheme=scheme)
+    n0, u0 = inputs.perturbed_field((nz, ny, nx), 0.02, 3.0, (0.01, -0.02, 0.005), seed=1)
+    for n in (4, 5, 7, 10):
+        one, _ = run(cfg, n0, u0, [1] * n)
+        for calls in ([n], [1, n - 1]):
+            many, _ = run(cfg, n0, u0, calls)
+            assert np.array_equal(one, many), (n, calls, int((one != many).sum()))
+
+
 def test_aa_runs_in_a_workspace_of_one_lattice(gpu):
     """A caller that gives an AA box no second lattice still gets its steps, in place."""
     cfg, n0, u0 = make((200, 90), order=2, scheme=AA)

@@ -257,7 +257,7 @@ typedef struct {
     double rho_ref;          /* deviation reference (1.0 if <= 0) */
     int tile_cols;           /* columns per tile, 0 = the largest that fits LDS with the halo */
     int halo;                /* steps per round = halo columns per side, 0 = 64 */
-    int block;               /* threads per workgroup, 0 = 1024 */
+    int block;               /* threads per workgroup, taken as 256, 512 or 1024 (0), the next that is not less */
     int use_graph;           /* capture lbm_batch_run's rounds into one HIP graph */
     double fugacity;         /* LBM_W_FD / LBM_W_BE only */
 } lbm_batch_options;

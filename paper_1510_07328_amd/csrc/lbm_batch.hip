@@ -18,7 +18,7 @@
 // Every cell update is the same collide() as the plain field kernels, so a tube
 // advanced here is bit-for-bit the tube advanced by lbm_step on an nx x 4 box.
 // Global traffic per lattice update drops by the factor of about H, and the
-// sweep is bound by LDS bandwidth and arithmetic rather than by HBM.
+// sweep is bound by vector issue rather than by HBM.
 #include <hip/hip_runtime.h>
 
 #include "lbm_batch.h"
@@ -33,84 +33,37 @@ constexpr int NY = 4;  // rows of every tube
 constexpr int kTubeThreads = 1024;  // per-tube kernels: one workgroup per tube
 using Lat = D2Q9;
 
-// LDS window layout: lds[(q * 4 + y) * WP + c], WP a power of two >= W (the
-// row stride, a template parameter so that cell -> (row, column) is a shift and
-// a mask).  Columns c >= W of a row are unused.
+// One round: each workgroup takes one tile of the active prefix, or, with a tile
+// list (list[0] tiles, their indices from list[1]), the tile the list names for it
+// (workgroups past the list's count return at once).  The window holds W = s + halo
+// columns (W <= WP).
 //
-// Natural-layout populations of cell (y, c): after an even number of AA steps
-// they sit in their own slots; after an odd number, g_a of the cell is in the
-// slot of -a at c - e_a (its own slot a where that crosses a window edge, which
-// is a wall).  EDGE selects the wall checks (only the first and last column of
-// the window need them).
-// Row-and-column bases of the rows y - 1, y, y + 1 (periodic in y); every
-// population's slot is one of them plus a compile-time offset (plane and x
-// shift), which the LDS instructions take as an immediate.
-template <int WP>
-struct RowBases {
-    int m, z, p;  // (y-1) WP + c, y WP + c, (y+1) WP + c
-    __device__ __forceinline__ RowBases(int y, int c)
-        : m(((y - 1) & (NY - 1)) * WP + c), z(y * WP + c), p(((y + 1) & (NY - 1)) * WP + c) {}
-    __device__ __forceinline__ int row(int dy) const { return dy < 0 ? m : (dy > 0 ? p : z); }
-};
-
-template <int WP, typename T, bool EDGE>
-__device__ __forceinline__ void load_cell(const T *__restrict__ lds, int W, int y, int c, bool odd,
-                                          T (&g)[Lat::Q]) {
-    constexpr int pl = NY * WP;
-    if (!odd) {
-#pragma unroll
-        for (int q = 0; q < Lat::Q; ++q) g[q] = lds[q * pl + y * WP + c];
-    } else if (!EDGE) {
-        const RowBases<WP> rb(y, c);
-#pragma unroll
-        for (int q = 0; q < Lat::Q; ++q)  // from the slot of -q at (y - e_y, c - e_x)
-            g[q] = lds[rb.row(-Lat::e[q][1]) + (Lat::opp[q] * pl - Lat::e[q][0])];
-    } else {
-#pragma unroll
-        for (int q = 0; q < Lat::Q; ++q) {
-            const int cs = c - Lat::e[q][0];
-            const int ys = (y - Lat::e[q][1]) & (NY - 1);
-            if (EDGE && (cs < 0 || cs >= W)) g[q] = lds[q * pl + y * WP + c];
-            else g[q] = lds[Lat::opp[q] * pl + ys * WP + cs];
-        }
-    }
-}
-
-template <int WP, typename T, bool EDGE>
-__device__ __forceinline__ void store_cell(T *__restrict__ lds, int W, int y, int c, bool odd, const T (&g)[Lat::Q]) {
-    constexpr int pl = NY * WP;
-    if (!odd) {
-#pragma unroll
-        for (int q = 0; q < Lat::Q; ++q) lds[Lat::opp[q] * pl + y * WP + c] = g[q];
-    } else if (!EDGE) {
-        const RowBases<WP> rb(y, c);
-#pragma unroll
-        for (int q = 0; q < Lat::Q; ++q)  // to slot q at (y + e_y, c + e_x)
-            lds[rb.row(Lat::e[q][1]) + (q * pl + Lat::e[q][0])] = g[q];
-    } else {
-#pragma unroll
-        for (int q = 0; q < Lat::Q; ++q) {
-            const int xt = c + Lat::e[q][0];
-            const int yt = (y + Lat::e[q][1]) & (NY - 1);
-            if (EDGE && (xt < 0 || xt >= W)) lds[Lat::opp[q] * pl + y * WP + c] = g[q];
-            else lds[q * pl + yt * WP + xt] = g[q];
-        }
-    }
-}
-
-// One round: each workgroup takes one tile of the active prefix, or, with a
-// tile list (list[0] tiles, their indices from list[1]), the tile the list
-// names for it (workgroups past the list's count return at once).  The window
-// holds W = s + halo columns (W <= WP); thread t handles the cells
-// t, t + blockDim, ... of the 4 x WP cell grid (row = cell / WP).
-template <int WP, typename T, bool O3>
-__global__ void __launch_bounds__(1024) k_batch_round(T *__restrict__ buf0, T *__restrict__ buf1,
-                                                      const BatchTube *__restrict__ tubes,
-                                                      const BatchTile *__restrict__ tiles,
-                                                      const int *__restrict__ list, int round, int H, Coef<T> c) {
-    static_assert(WP % 64 == 0, "a wavefront's 64 cells must lie in one window row");
-    __shared__ T lds[Lat::Q * NY * WP];
-    constexpr int CELLS = NY * WP;
+// LDS: eight planes (the rest population never leaves its cell and stays in a
+// register) of four rows of WP + 2 columns; column x of the window is at x + 1,
+// and columns 0 and W + 1 are ghosts.  After an even number of AA steps the
+// populations of a cell sit in its own slots; after an odd number g_q is in the
+// slot of -q at x - e_q.  The window's edges are walls: the cell at an edge, whose
+// link q leaves the window, writes that population a second time, after an even
+// step into the ghost column, where its reflection is read from, and after an odd
+// step into its own slot -q.  Every cell so reads and writes by one rule, at a
+// lane's column plus compile-time offsets (the planes and rows are the LDS
+// instructions' immediate offsets), and only a wavefront that holds an edge does
+// the extra writes: about 103 vector instructions per update, of which 99 are the
+// collision (123 before, with the slot addresses formed in every step and the two
+// edge wavefronts of a row selecting them per lane).  512 tubes of 256 to 8192
+// columns, 4 nx steps each: 273 -> 214 ms, 350 GLUPS: vector issue with the halo
+// columns (512 of 448) counted.
+// Cell k of a thread is k BLOCK + threadIdx.x of the 4 x WP grid (row = cell / WP).
+template <int WP, int BLOCK, typename T, bool O3>
+__global__ void __launch_bounds__(BLOCK) k_batch_round(T *__restrict__ buf0, T *__restrict__ buf1,
+                                                       const BatchTube *__restrict__ tubes,
+                                                       const BatchTile *__restrict__ tiles,
+                                                       const int *__restrict__ list, int round, int H, Coef<T> c) {
+    static_assert(WP % 64 == 0 && BLOCK % 64 == 0, "a wavefront's 64 cells lie in one window row");
+    static_assert(BLOCK % WP == 0 || WP % BLOCK == 0, "a thread's cells share a column or lie at fixed rows");
+    constexpr int CPT = NY * WP / BLOCK, RS = WP + 2, PL = NY * RS;
+    static_assert(CPT >= 1, "no more threads than cells");
+    __shared__ T lds[(Lat::Q - 1) * PL];
     int ti = blockIdx.x;
     if (list) {
         if (ti >= list[0]) return;
@@ -136,51 +89,92 @@ __global__ void __launch_bounds__(1024) k_batch_round(T *__restrict__ buf0, T *_
     const T *__restrict__ gsrc = src + tb.off + w0;
     T *__restrict__ gdst = dst + tb.off + w0;
 
-    // load the window (natural layout), coalesced along x
-    for (int i = threadIdx.x; i < Lat::Q * CELLS; i += blockDim.x) {
-        const int qy = i / WP, x = i & (WP - 1);
-        if (x < W) lds[i] = gsrc[(int64_t)(qy >> 2) * gpl + (int64_t)(qy & 3) * tb.nx + x];
-    }
-    __syncthreads();
+    const int x = threadIdx.x % WP, y0 = threadIdx.x / WP;  // of cell 0
+    T *rows[NY];  // row (y0 + j) mod 4 at column x
+#pragma unroll
+    for (int j = 0; j < NY; ++j) rows[j] = lds + ((y0 + j) & (NY - 1)) * RS + x + 1;
+    // slot q of the cell (dx, dy) from cell k (k, dy and dx are compile-time constants)
+    auto slot = [&](int k, int q, int dx, int dy) -> T & {
+        if constexpr (BLOCK >= WP) {
+            return rows[(k * (BLOCK / WP) + dy) & (NY - 1)][(q - 1) * PL + dx];
+        } else {  // y0 = 0: the row is a constant
+            return lds[threadIdx.x + (1 + (k * BLOCK) % WP + (((k * BLOCK) / WP + dy) & (NY - 1)) * RS + (q - 1) * PL + dx)];
+        }
+    };
+    auto col = [&](int k) { return BLOCK >= WP ? x : (int)threadIdx.x + (k * BLOCK) % WP; };
+    auto row = [&](int k) { return BLOCK >= WP ? y0 + k * (BLOCK / WP) : (k * BLOCK) / WP; };
 
-    // The wall checks concern only odd steps (even steps use the cell's own
-    // slots) and only the window's first and last columns.  The choice is made
-    // per wavefront (its 64 cells lie in one row, WP being a multiple of 64), so
-    // that a wavefront runs one path: a per-lane branch made the two wavefronts
-    // of a row that hold an end column run the whole collision twice.
-    for (int step = 0; step < h; ++step) {
-        const bool odd = step & 1;
-        for (int cell = threadIdx.x; cell < CELLS; cell += blockDim.x) {
-            const int y = cell / WP, x = cell & (WP - 1);
-            const int x0 = __builtin_amdgcn_readfirstlane(x - (int)(threadIdx.x & 63));  // the wavefront's first column
-            if (x >= W) continue;
-            T g[Lat::Q];
-            if (!odd) {
-                load_cell<WP, T, false>(lds, W, y, x, false, g);
+    T rest[CPT];
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) {
+        rest[k] = T(0);
+        if (col(k) < W) {
+            const int64_t o = (int64_t)row(k) * tb.nx + col(k);
+            rest[k] = gsrc[o];
+#pragma unroll
+            for (int q = 1; q < Lat::Q; ++q) slot(k, q, 0, 0) = gsrc[q * gpl + o];
+        }
+    }
+
+    for (int step = 0; step < h; step += 2) {
+#pragma unroll
+        for (int k = 0; k < CPT; ++k) {
+            const int xk = col(k);
+            const bool le = xk == 0, re = xk == W - 1;
+            if (xk < W) {
+                T g[Lat::Q];
+                g[0] = rest[k];
+#pragma unroll
+                for (int q = 1; q < Lat::Q; ++q) g[q] = slot(k, q, 0, 0);
                 collide<Lat, T, O3>(g, c);
-                store_cell<WP, T, false>(lds, W, y, x, false, g);
-            } else if (x0 > 0 && x0 + 63 < W - 1) {
-                load_cell<WP, T, false>(lds, W, y, x, true, g);
-                collide<Lat, T, O3>(g, c);
-                store_cell<WP, T, false>(lds, W, y, x, true, g);
-            } else {
-                load_cell<WP, T, true>(lds, W, y, x, true, g);
-                collide<Lat, T, O3>(g, c);
-                store_cell<WP, T, true>(lds, W, y, x, true, g);
+                rest[k] = g[0];
+#pragma unroll
+                for (int q = 1; q < Lat::Q; ++q) slot(k, Lat::opp[q], 0, 0) = g[q];
+                if (__builtin_amdgcn_ballot_w64(le || re) != 0) {
+#pragma unroll
+                    for (int q = 1; q < Lat::Q; ++q)
+                        if ((Lat::e[q][0] < 0 && le) || (Lat::e[q][0] > 0 && re))
+                            slot(k, q, Lat::e[q][0], Lat::e[q][1]) = g[q];
+                }
             }
         }
         __syncthreads();
+        if (step + 1 < h) {
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) {
+                const int xk = col(k);
+                const bool le = xk == 0, re = xk == W - 1;
+                if (xk < W) {
+                    T g[Lat::Q];
+                    g[0] = rest[k];
+#pragma unroll
+                    for (int q = 1; q < Lat::Q; ++q) g[q] = slot(k, Lat::opp[q], -Lat::e[q][0], -Lat::e[q][1]);
+                    collide<Lat, T, O3>(g, c);
+                    rest[k] = g[0];
+#pragma unroll
+                    for (int q = 1; q < Lat::Q; ++q) slot(k, q, Lat::e[q][0], Lat::e[q][1]) = g[q];
+                    if (__builtin_amdgcn_ballot_w64(le || re) != 0) {
+#pragma unroll
+                        for (int q = 1; q < Lat::Q; ++q)
+                            if ((Lat::e[q][0] < 0 && le) || (Lat::e[q][0] > 0 && re)) slot(k, Lat::opp[q], 0, 0) = g[q];
+                    }
+                }
+            }
+            __syncthreads();
+        }
     }
 
     // write the tile's own columns back in natural layout
     const bool odd_end = h & 1;
-    for (int cell = threadIdx.x; cell < CELLS; cell += blockDim.x) {
-        const int y = cell / WP, x = cell & (WP - 1);
-        if (x < hl || x >= hl + tl.s) continue;
-        T g[Lat::Q];
-        load_cell<WP, T, true>(lds, W, y, x, odd_end, g);
 #pragma unroll
-        for (int q = 0; q < Lat::Q; ++q) gdst[(int64_t)q * gpl + (int64_t)y * tb.nx + x] = g[q];
+    for (int k = 0; k < CPT; ++k) {
+        const int xk = col(k);
+        if (xk < hl || xk >= hl + tl.s) continue;
+        const int64_t o = (int64_t)row(k) * tb.nx + xk;
+        gdst[o] = rest[k];
+#pragma unroll
+        for (int q = 1; q < Lat::Q; ++q)
+            gdst[q * gpl + o] = odd_end ? slot(k, Lat::opp[q], -Lat::e[q][0], -Lat::e[q][1]) : slot(k, q, 0, 0);
     }
 }
 
@@ -439,28 +433,44 @@ __global__ void __launch_bounds__(256) k_batch_set_steps(BatchTube *__restrict__
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-template <int WP, typename T>
+template <int WP, int BLOCK, typename T>
 hipError_t batch_round_wp(void *b0, void *b1, const BatchTube *tubes, const BatchTile *tiles, const int *list,
-                          int ntiles, int round, int H, int block, const Coef<T> &c, bool o3, hipStream_t s) {
+                          int ntiles, int round, int H, const Coef<T> &c, bool o3, hipStream_t s) {
     if (o3)
-        hipLaunchKernelGGL((k_batch_round<WP, T, true>), dim3(ntiles), dim3(block), 0, s, (T *)b0, (T *)b1, tubes,
+        hipLaunchKernelGGL((k_batch_round<WP, BLOCK, T, true>), dim3(ntiles), dim3(BLOCK), 0, s, (T *)b0, (T *)b1, tubes,
                            tiles, list, round, H, c);
     else
-        hipLaunchKernelGGL((k_batch_round<WP, T, false>), dim3(ntiles), dim3(block), 0, s, (T *)b0, (T *)b1, tubes,
+        hipLaunchKernelGGL((k_batch_round<WP, BLOCK, T, false>), dim3(ntiles), dim3(BLOCK), 0, s, (T *)b0, (T *)b1, tubes,
                            tiles, list, round, H, c);
     return hipGetLastError();
 }
 
-// The window stride: the smallest power of two that holds W columns.
+// The window stride: the smallest of 128, 256 and 512 that holds W columns.  The
+// workgroup: the smallest of 256, 512 and 1024 threads that is at least `block`
+// (at most one thread per cell of the window).
 template <typename T>
 hipError_t batch_round_t(void *b0, void *b1, const BatchTube *tubes, const BatchTile *tiles, const int *list,
                          int ntiles, int round, int H, int W, int block, const Model &m, double rho_ref,
                          hipStream_t s) {
     const Coef<T> c = make_coef<T>(m, 1.0, rho_ref);
     const bool o3 = has_third_order(m);
-    if (W <= 128) return batch_round_wp<128, T>(b0, b1, tubes, tiles, list, ntiles, round, H, block, c, o3, s);
-    if (W <= 256) return batch_round_wp<256, T>(b0, b1, tubes, tiles, list, ntiles, round, H, block, c, o3, s);
-    if (W <= 512) return batch_round_wp<512, T>(b0, b1, tubes, tiles, list, ntiles, round, H, block, c, o3, s);
+    const int bl = block <= 256 ? 0 : block <= 512 ? 1 : 2;
+#define ROUND(WP, BL) return batch_round_wp<WP, BL, T>(b0, b1, tubes, tiles, list, ntiles, round, H, c, o3, s)
+    if (W <= 128) {
+        if (bl == 0) ROUND(128, 256);
+        ROUND(128, 512);
+    }
+    if (W <= 256) {
+        if (bl == 0) ROUND(256, 256);
+        if (bl == 1) ROUND(256, 512);
+        ROUND(256, 1024);
+    }
+    if (W <= 512) {
+        if (bl == 0) ROUND(512, 256);
+        if (bl == 1) ROUND(512, 512);
+        ROUND(512, 1024);
+    }
+#undef ROUND
     return hipErrorInvalidValue;
 }
 

@@ -27,6 +27,36 @@ struct LdsLimit {
     }
 };
 
+// One lattice as a buffer: a slot at a wave-uniform byte offset plus a lane's.  The
+// hardware drops a store whose lane offset lies past the buffer, so a lane that has
+// nothing to write takes kNoStore instead of a branch; behind a branch the compiler
+// cannot count the stores in flight, and the wait for the next row's loads becomes
+// one for every store.
+constexpr uint32_t kNoStore = 0xffffffffu;
+template <typename T>
+struct LatticeBuffer {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ LatticeBuffer(const T *p, uint32_t bytes)
+        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(p), 0, (int)bytes, 0x00020000)) {}
+    __device__ __forceinline__ T load(uint32_t uniform, uint32_t lane) const {
+        if constexpr (sizeof(T) == 8)
+            return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)lane, (int)uniform, 0));
+        else
+            return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)lane, (int)uniform, 0));
+    }
+    __device__ __forceinline__ void store(uint32_t uniform, uint32_t lane, T v) const {
+        if constexpr (sizeof(T) == 8) {
+            typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)lane, (int)uniform, 0);
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)lane, (int)uniform, 0);
+        }
+    }
+};
+// Waits for the loads in flight (vmcnt 0).  Before a loop that keeps stores in
+// flight: else the waits at its head count as on entry, where no store follows the loads.
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+
 constexpr int kMultiTail = 24;  // the last steps of a call, planned together
 
 struct MultiPlan {
@@ -47,7 +77,6 @@ int multi_depth(const MultiPlan &p, int64_t n, int odd);
 // H steps from src into dst (another lattice), both in natural layout.
 hipError_t launch_multi(int fp64, int H, const void *src, void *dst, const uint32_t *lm, const Box &b, const Model &m,
                         double tau, double rho_ref, const double *F, int ly, hipStream_t s);
-
 
 // Two steps of a periodic d3v19 box per pass (lbm_multi3.hip), segments of lz
 // planes (multi3_plan: 0 where single steps are faster).

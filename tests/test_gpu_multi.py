@@ -112,6 +112,25 @@ def test_periodic_d3v19_boxes(gpu, shape, order, precision, scheme):
             assert np.array_equal(one, many), (n, calls, int((one != many).sum()))
 
 
+@pytest.mark.parametrize("scheme", [PUSH, AA])
+@pytest.mark.parametrize("shape,order,precision", [
+    ((130, 125, 128), 2, lbm.LBM_FP32_DEV),  # short last strip, group and segment
+    ((186, 84, 131), 3, lbm.LBM_FP32_DEV),   # exact strips and groups
+    ((63, 141, 114), 2, lbm.LBM_FP64),       # one column and three rows left over
+    ((124, 60, 137), 3, lbm.LBM_FP64),
+])
+def test_large_periodic_d3v19_boxes(gpu, shape, order, precision, scheme):
+    """Boxes of 2 million float32 cells (or as many bytes in float64): a wavefront's rows in pairs,
+    lanes without an output store past the buffer's end."""
+    nx, ny, nz = shape
+    cfg = lbm.make_config("d3v19", shape=shape, order=order, tau=0.7, precision=precision, scheme=scheme)
+    n0, u0 = inputs.perturbed_field((nz, ny, nx), 0.02, 3.0, (0.01, -0.02, 0.005), seed=2)
+    for n in (4, 9):
+        one, _ = run(cfg, n0, u0, [1] * n)
+        many, _ = run(cfg, n0, u0, [n])
+        assert np.array_equal(one, many), (n, int((one != many).sum()))
+
+
 def test_aa_runs_in_a_workspace_of_one_lattice(gpu):
     """A caller that gives an AA box no second lattice still gets its steps, in place."""
     cfg, n0, u0 = make((200, 90), order=2, scheme=AA)

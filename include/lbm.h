@@ -150,10 +150,10 @@ lbm_status lbm_coefficients(const lbm_config *cfg, double *out, int cap, int *n_
 
 /* Bytes of device workspace lbm_init takes for cfg: two lattices for the push
  * scheme, one for AA, plus reduction scratch and the staging area of the host
- * lbm_moments, about 4 MB.  d2v9 boxes, and d3v19 boxes without walls,
- * obstacles or a force, with one weight for all cells and a lattice below 4 GiB
- * run calls of several steps as passes of several steps
- * from one lattice into another; for AA the value then holds a second lattice
+ * lbm_moments, about 4 MB.  d2v9 boxes, and d3v19 boxes without obstacles or a
+ * force, with one weight for all cells and a lattice below 4 GiB run calls of
+ * several steps as passes of several steps from one lattice into another; for AA
+ * the value then holds a second lattice
  * (which overlaps the staging area).  lbm_init accepts an AA workspace without
  * it, down to one lattice and the staging area: steps then run one by one, in
  * place, with the same results.  Host only. */

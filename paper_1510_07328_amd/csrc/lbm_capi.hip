@@ -112,8 +112,7 @@ lbm_status check_config(const lbm_config *cfg, Model *m, Layout *lay) {
     lay->stage_rows = (int)srows;
     const size_t stage = align_up((size_t)srows * row_bytes);
     lay->min_total = lay->total = lay->stage_off + stage;
-    const bool links = lay->porous || cfg->bc[0] || cfg->bc[1] || cfg->bc[2];
-    lay->multi = multi_eligible(cfg->lattice, m->local != 0, links, lay->plane, lay->elt);
+    lay->multi = multi_eligible(cfg->lattice, m->local != 0, lay->porous, lay->plane, lay->elt);
     // AA: the second lattice of the passes, which between calls is free for the staging
     if (lay->multi && lay->nlat == 1)
         lay->total = lay->stage_off + (lay->lattice_bytes > stage ? lay->lattice_bytes : stage);
@@ -338,7 +337,7 @@ lbm_status lbm_init(const lbm_config *cfg, void *workspace, size_t bytes, void *
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         const bool links = lay.porous || c->box.bbx || c->box.bby;
         if (m.D == 3) {
-            c->lz = multi3_plan(cfg->nx, cfg->ny, cfg->nz, c->fp64, cus);
+            c->lz = multi3_plan(cfg->nx, cfg->ny, cfg->nz, c->fp64, links ? 2 : c->box.bbz ? 1 : 0, cus);
         } else {
             c->plan = multi_plan(cfg->nx, cfg->ny, c->fp64, links, lay.nlat == 2, cus);
             c->tile = tile_plan(cfg->nx, cfg->ny, c->box.bbx, c->box.bby, lay.porous, c->fp64, cus);

@@ -68,8 +68,8 @@ struct MultiPlan {
     signed char next[kMultiTail + 1][2] = {};
 };
 
-// d2v9, or d3v19 without walls, solids or a force; one weight for all cells, a lattice below 4 GiB
-bool multi_eligible(int lattice, bool local, bool links, int64_t plane, size_t elt);
+// d2v9, or d3v19 without solids or a force; one weight for all cells, a lattice below 4 GiB
+bool multi_eligible(int lattice, bool local, bool porous, int64_t plane, size_t elt);
 // links: walls or solid cells; single: a single step may stand between passes (push; an AA step changes the layout)
 MultiPlan multi_plan(int nx, int ny, int fp64, bool links, bool single, int cus);
 // The next launch of n > 0 steps that are to take an even or odd number of launches.
@@ -78,9 +78,10 @@ int multi_depth(const MultiPlan &p, int64_t n, int odd);
 hipError_t launch_multi(int fp64, int H, const void *src, void *dst, const uint32_t *lm, const Box &b, const Model &m,
                         double tau, double rho_ref, const double *F, int ly, hipStream_t s);
 
-// Two steps of a periodic d3v19 box per pass (lbm_multi3.hip), segments of lz
+// Two steps of a d3v19 box per pass (lbm_multi3.hip), segments of lz
 // planes (multi3_plan: 0 where single steps are faster).
-int multi3_plan(int nx, int ny, int nz, int fp64, int cus);
+// walls: 0 none, 1 in z only, 2 in x or y
+int multi3_plan(int nx, int ny, int nz, int fp64, int walls, int cus);
 hipError_t launch_multi3(int fp64, const void *src, void *dst, const Box &b, const Model &m, double tau,
                          double rho_ref, int lz, hipStream_t s);
 

@@ -303,10 +303,10 @@ constexpr int kDepths[] = {2, 3, 4, 6};
 
 }  // namespace
 
-bool multi_eligible(int lattice, bool local, bool links, int64_t plane, size_t elt) {
+bool multi_eligible(int lattice, bool local, bool porous, int64_t plane, size_t elt) {
     // 32-bit byte offsets from the lattice base, as in the single-step kernels
     const int q = lattice == LBM_D2V9 ? D2Q9::Q : D3Q19::Q;
-    return !local && (lattice == LBM_D2V9 || (lattice == LBM_D3V19 && !links)) &&
+    return !local && (lattice == LBM_D2V9 || (lattice == LBM_D3V19 && !porous)) &&
            (uint64_t)q * (uint64_t)plane * elt < (uint64_t(1) << 32);
 }
 

@@ -1,4 +1,4 @@
-// Two lattice BGK steps of a periodic d3v19 box in one pass over memory.
+// Two lattice BGK steps of a d3v19 box in one pass over memory.
 //
 // One step per kernel moves 152 B per update in float32 and is bound by that.
 // Here a workgroup marches along z over a window of 64 columns (the lanes) and 16
@@ -66,18 +66,22 @@ constexpr int yslot(int q) {
 }
 constexpr int NYQ = yslot(Q);
 
-// W wavefronts of R rows.  PACED: rows in pairs and every store issued (see k_multi3).
-template <typename T, bool PACED>
+// OPEN: a row per wavefront; PACED: rows in pairs and every store issued; WALLED: a
+// row per wavefront and walls on any axis.
+enum Kind3 { OPEN, PACED, WALLED };
+// W wavefronts of R rows, B LDS buffers
+template <typename T, Kind3 KIND>
 struct Rows3 {
-    static constexpr int W = PACED || sizeof(T) == 8 ? 8 : 16, R = PACED && sizeof(T) == 4 ? 2 : 1, n = W * R;
-    static constexpr size_t lds = sizeof(T) * 2 * NYQ * W * 64;
+    static constexpr int W = KIND == PACED || sizeof(T) == 8 ? 8 : 16, R = KIND == PACED && sizeof(T) == 4 ? 2 : 1;
+    static constexpr int n = W * R, B = KIND == WALLED ? 3 : 2;
+    static constexpr size_t lds = sizeof(T) * B * NYQ * W * 64;
 };
 
-template <typename T, bool O3, bool PACED>
-__global__ void __launch_bounds__((64 * Rows3<T, PACED>::W)) k_multi3(const T *__restrict__ src,
+template <typename T, bool O3, Kind3 KIND>
+__global__ void __launch_bounds__((64 * Rows3<T, KIND>::W)) k_multi3(const T *__restrict__ src,
                                                                             T *__restrict__ dst, Box b, Coef<T> c,
                                                                             int strips, int groups, int lz) {
-    constexpr int W = Rows3<T, PACED>::W, R = Rows3<T, PACED>::R, NW = W * R;
+    constexpr int W = Rows3<T, KIND>::W, R = Rows3<T, KIND>::R, NW = W * R;
     extern __shared__ unsigned char smem3[];
     T(*lds)[NYQ][W][64] = reinterpret_cast<T(*)[NYQ][W][64]>(smem3);
     // neighbouring windows share lines: a contiguous run of them per XCD
@@ -108,6 +112,14 @@ __global__ void __launch_bounds__((64 * Rows3<T, PACED>::W)) k_multi3(const T *_
         oyp[r] = y == ny - 1 ? off(0) : oy[r] + rowb;
         out[r] = k >= 1 && k < NW - 1 && yo < ny;
     }
+    // WALLED: does link q of this lane's cell leave the box through a wall; zm, zp: its plane lies there
+    const bool wxm = b.bbx && x == 0, wxp = b.bbx && x == nx - 1;
+    const bool wym = b.bby && oy[0] == 0u, wyp = b.bby && oy[0] == off(ny - 1) * rowb;
+    const bool anyxy = KIND == WALLED && (wym || wyp || __builtin_amdgcn_ballot_w64(wxm || wxp) != 0);
+    auto leaves = [&](int q, bool zm, bool zp) {
+        const int ex = Lat::e[q][0], ey = Lat::e[q][1], ez = Lat::e[q][2];
+        return (ex < 0 && wxm) || (ex > 0 && wxp) || (ey < 0 && wym) || (ey > 0 && wyp) || (ez < 0 && zm) || (ez > 0 && zp);
+    };
     const bool outx = lane >= 1 && lane < 63 && xo < nx;
 
     T a[R][Q], b1[R][Q];  // ez = 0 of plane z - 1; ez = 1 moved from planes z - 2 (a) and z - 1 (b1)
@@ -130,13 +142,14 @@ __global__ void __launch_bounds__((64 * Rows3<T, PACED>::W)) k_multi3(const T *_
         for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int q = 0; q < Q; ++q) g[r][q] = nxt[r][q];
+        const int zi = z;
         z = z + 1 == nz ? 0 : z + 1;
         fetch(z);  // after the last plane: one that is not used
 #pragma unroll
         for (int r = 0; r < R; ++r) collide<Lat, T, O3>(g[r], c);
         // move the plane's populations in x, and in y: between a wavefront's rows in its
         // registers, to its neighbours through LDS
-        T(*buf)[W][64] = lds[i & 1];
+        T(*buf)[W][64] = lds[KIND == WALLED ? i % 3 : i & 1];
 #pragma unroll
         for (int q = 1; q < Q; ++q) {
 #pragma unroll
@@ -151,6 +164,32 @@ __global__ void __launch_bounds__((64 * Rows3<T, PACED>::W)) k_multi3(const T *_
             const T v = buf[yslot(q)][(w - ey) & (W - 1)][lane];
             if (R > 1) g[ey > 0 ? R - 1 : 0][q] = g[ey > 0 ? 0 : R - 1][q];
             g[ey > 0 ? 0 : R - 1][q] = v;
+        }
+        if constexpr (KIND == WALLED) {
+            // Populations that cannot arrive: the cell's own of the opposite link, as collided.
+            // Those sit one lane off in a register, or in the cell's row of the LDS buffer of
+            // its plane (the third buffer keeps the previous plane's until all have read it).
+            const int zj = zi == 0 ? nz - 1 : zi - 1;
+            const bool am = b.bbz && zi == 0, ap = b.bbz && zi == nz - 1, bm = b.bbz && zj == 0, bp = b.bbz && zj == nz - 1;
+            if (anyxy || am || ap || bm || bp) {
+                T(*old)[W][64] = lds[(i + 2) % 3];
+                auto own = [&](int p, T moved, T(*rows)[W][64]) {
+                    return Lat::e[p][1] != 0 ? rows[yslot(p)][w][(lane + Lat::e[p][0]) & 63] : from_x(moved, -Lat::e[p][0]);
+                };
+#pragma unroll
+                for (int q = 1; q < Q; ++q) {
+                    const int p = Lat::opp[q], ez = Lat::e[q][2];
+                    if (ez > 0) {  // q enters plane zi from below, p plane zi - 1 from above
+                        const T u = own(p, g[0][p], buf), v = own(q, b1[0][q], old);
+                        if (leaves(q, bm, bp)) g[0][p] = v;
+                        if (leaves(p, am, ap)) b1[0][q] = u;
+                    } else if (ez == 0 && q < p) {
+                        const T u = own(p, g[0][p], buf), v = own(q, g[0][q], buf);
+                        if (leaves(p, am, ap)) g[0][q] = u;
+                        if (leaves(q, am, ap)) g[0][p] = v;
+                    }
+                }
+            }
         }
         // the previous plane is complete with the ez = -1 populations of this one
 #pragma unroll
@@ -179,11 +218,23 @@ __global__ void __launch_bounds__((64 * Rows3<T, PACED>::W)) k_multi3(const T *_
             const off zz = Lat::e[q][2] < 0 ? ozm : (Lat::e[q][2] > 0 ? ozp : oz);
             to.store(off(q) * pl + zz + yy, none | xx, g[r][q]);
         };
-        if constexpr (PACED) {
+        const bool zm = b.bbz && zc == 0, zp = b.bbz && zc == nz - 1;
+        if constexpr (KIND == PACED) {
 #pragma unroll
             for (int q = 0; q < Q; ++q)
 #pragma unroll
                 for (int r = 0; r < R; ++r) store(q, r, outx && out[r] ? 0u : kNoStore);
+        } else if (KIND == WALLED && (anyxy || zm || zp)) {
+            if (outx && out[0]) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const off xx = Lat::e[q][0] < 0 ? oxm : (Lat::e[q][0] > 0 ? oxp : ox);
+                    const off yy = Lat::e[q][1] < 0 ? oym[0] : (Lat::e[q][1] > 0 ? oyp[0] : oy[0]);
+                    const off zz = Lat::e[q][2] < 0 ? ozm : (Lat::e[q][2] > 0 ? ozp : oz);
+                    to.store(0u, leaves(q, zm, zp) ? off(Lat::opp[q]) * pl + oz + oy[0] + ox : off(q) * pl + zz + yy + xx,
+                             g[0][q]);
+                }
+            }
         } else if (outx && out[0]) {
 #pragma unroll
             for (int q = 0; q < Q; ++q) store(q, 0, 0u);
@@ -197,16 +248,16 @@ __global__ void __launch_bounds__((64 * Rows3<T, PACED>::W)) k_multi3(const T *_
     for (int i = 2; i < z1 - z0 + 2; ++i) advance(i, std::true_type{});
 }
 
-template <typename T, bool O3, bool PACED>
-hipError_t launch_p(const void *src, void *dst, const Box &b, const Coef<T> &c, int lz, hipStream_t s) {
-    using Rows = Rows3<T, PACED>;
+template <typename T, bool O3, Kind3 KIND>
+hipError_t launch_k(const void *src, void *dst, const Box &b, const Coef<T> &c, int lz, hipStream_t s) {
+    using Rows = Rows3<T, KIND>;
     const int strips = (b.nx + 61) / 62, groups = (b.ny + Rows::n - 3) / (Rows::n - 2), segs = (b.nz + lz - 1) / lz;
     const int64_t blocks = (int64_t)strips * groups * segs;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     static LdsLimit limit;
-    const hipError_t e = limit.raise((const void *)k_multi3<T, O3, PACED>, (int)Rows::lds);
+    const hipError_t e = limit.raise((const void *)k_multi3<T, O3, KIND>, (int)Rows::lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_multi3<T, O3, PACED>), dim3((unsigned)blocks), dim3(64 * Rows::W), Rows::lds, s,
+    hipLaunchKernelGGL((k_multi3<T, O3, KIND>), dim3((unsigned)blocks), dim3(64 * Rows::W), Rows::lds, s,
                        (const T *)src, (T *)dst, b, c, strips, groups, lz);
     return hipGetLastError();
 }
@@ -216,8 +267,9 @@ bool paced(double size) { return size >= 2e6; }
 
 template <typename T, bool O3>
 hipError_t launch_t(const void *src, void *dst, const Box &b, const Coef<T> &c, int lz, hipStream_t s) {
-    if (paced((double)b.nx * b.ny * b.nz * (sizeof(T) / 4))) return launch_p<T, O3, true>(src, dst, b, c, lz, s);
-    return launch_p<T, O3, false>(src, dst, b, c, lz, s);
+    if (b.bbx || b.bby || b.bbz) return launch_k<T, O3, WALLED>(src, dst, b, c, lz, s);
+    if (paced((double)b.nx * b.ny * b.nz * (sizeof(T) / 4))) return launch_k<T, O3, PACED>(src, dst, b, c, lz, s);
+    return launch_k<T, O3, OPEN>(src, dst, b, c, lz, s);
 }
 
 }  // namespace
@@ -232,17 +284,25 @@ hipError_t launch_t(const void *src, void *dst, const Box &b, const Coef<T> &c, 
 // 331 (414 before, with branches and rows of their own), 256 x 256 x 60 115: 82 (95),
 // 160^3 137: 79 (81), 200 x 100 x 150 102: 73 (78), 128^3 82: 49.5 (52), 64^3 22: 9.4
 // (9.8), 40 x 40 x 200 37: 10.8 (11.1); float64 256^3 1018: 690 (707).
-int multi3_plan(int nx, int ny, int nz, int fp64, int cus) {
+// With walls a wavefront that holds one reads its own populations back: a plane takes
+// 4.2 us where only z has walls (its first and last planes), 6.0 where every plane has
+// some (20 spilled registers at 16 wavefronts of 128; float64 3.6).  Walls in x / in z:
+// 256^3 514: 487 / 434, 128^3 85: 77 / 59, 64^3 22: 16 / 12, 200 x 100 x 150 101:
+// 116 (single steps are kept) / 85; float64 100^3 68: 50 / 49.  A single step takes 8 us
+// for a start there, and large boxes take passes only for a clear gain.
+int multi3_plan(int nx, int ny, int nz, int fp64, int walls, int cus) {
     if (cus <= 0) cus = 256;
     const int nw = fp64 ? 8 : 16;
     const double cells = (double)nx * ny * nz, size = cells * (fp64 ? 2 : 1);
-    const double plane = !paced(size) ? 3.1 + 2.8 * size / 2e6 : fp64 ? 5.1 : 5.8;
+    const bool pace = paced(size) && !walls;
+    const double first = !walls ? 3.1 : fp64 ? 3.6 : walls == 1 ? 4.2 : 6.0, fill = size < 2e6 ? size / 2e6 : 1.0;
+    const double plane = pace ? (fp64 ? 5.1 : 5.8) : first + (walls && fp64 ? 1.8 : 2.8) * fill;
     const int64_t windows = (int64_t)((nx + 61) / 62) * ((ny + nw - 3) / (nw - 2));
     int best = 0;
-    double least = 2.0 * (5.0 + 38e-6 * size);
+    double least = 2.0 * ((walls ? 8.0 : 5.0) + 38e-6 * size) * (walls && size > 1e6 ? 0.85 : 1.0);
     for (int lz = 1; lz <= 64 && lz <= nz; ++lz) {
         const int64_t blocks = windows * ((nz + lz - 1) / lz), rounds = (blocks + cus - 1) / cus;
-        const double t = 4.0 + (double)rounds * (lz + 2) * plane * (paced(size) ? 1.0 + 0.004 * lz : 1.0);
+        const double t = 4.0 + (double)rounds * (lz + 2) * plane * (pace ? 1.0 + 0.004 * lz : 1.0);
         if (t < least) {
             least = t;
             best = lz;
@@ -253,7 +313,7 @@ int multi3_plan(int nx, int ny, int nz, int fp64, int cus) {
 
 hipError_t launch_multi3(int fp64, const void *src, void *dst, const Box &b, const Model &m, double tau,
                          double rho_ref, int lz, hipStream_t s) {
-    if (lz < 1 || b.bbx || b.bby || b.bbz) return hipErrorInvalidValue;
+    if (lz < 1) return hipErrorInvalidValue;
     if (fp64) {
         const Coef<double> c = make_coef<double>(m, tau, rho_ref);
         return has_third_order(m) ? launch_t<double, true>(src, dst, b, c, lz, s) : launch_t<double, false>(src, dst, b, c, lz, s);

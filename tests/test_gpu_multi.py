@@ -131,6 +131,29 @@ def test_large_periodic_d3v19_boxes(gpu, shape, order, precision, scheme):
         assert np.array_equal(one, many), (n, int((one != many).sum()))
 
 
+@pytest.mark.parametrize("scheme", [PUSH, AA])
+@pytest.mark.parametrize("precision", [lbm.LBM_FP32_DEV, lbm.LBM_FP64])
+@pytest.mark.parametrize("shape,bc,order", [
+    ((70, 45, 33), (1, 0, 0), 2),
+    ((64, 31, 40), (0, 1, 0), 3),
+    ((33, 60, 21), (0, 0, 1), 2),
+    ((62, 42, 36), (1, 1, 1), 3),    # walls at the ends of exact strips and groups
+    ((125, 16, 50), (1, 0, 1), 2),
+    ((40, 3, 90), (0, 1, 1), 2),
+])
+def test_walled_d3v19_boxes(gpu, shape, bc, order, precision, scheme):
+    """Two steps per pass with walls on one axis, on two and on all: links reflected on planes, edges and
+    corners, in both steps of the pass and across segments."""
+    nx, ny, nz = shape
+    cfg = lbm.make_config("d3v19", shape=shape, bc=bc, order=order, tau=0.7, precision=precision, scheme=scheme)
+    n0, u0 = inputs.perturbed_field((nz, ny, nx), 0.02, 3.0, (0.01, -0.02, 0.005), seed=3)
+    for n in (4, 5, 7, 12):
+        one, _ = run(cfg, n0, u0, [1] * n)
+        for calls in ([n], [1, n - 1]):
+            many, _ = run(cfg, n0, u0, calls)
+            assert np.array_equal(one, many), (n, calls, int((one != many).sum()))
+
+
 def test_aa_runs_in_a_workspace_of_one_lattice(gpu):
     """A caller that gives an AA box no second lattice still gets its steps, in place."""
     cfg, n0, u0 = make((200, 90), order=2, scheme=AA)

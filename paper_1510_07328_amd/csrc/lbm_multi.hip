@@ -25,9 +25,9 @@
 //
 // Bound: vector issue for deep pipelines (102 instructions per update, 6 of them
 // lane shifts; 256 CUs x 64 lanes), memory for H = 2 and 3; 2048^2 float32 47.9
-// -> 18.5 us per step, 4096^2 262 -> 67, 2048^2 float64 115 -> 28.  Registers:
+// -> 17.7 us per step, 4096^2 262 -> 63, 2048^2 float64 115 -> 28.  Registers:
 // 9 values per level and 9 of the next row; periodic float32 kernels are held to
-// 128 VGPRs (4 wavefronts per SIMD: 4096^2 68.8 -> 67.1 us), float64 to 256.
+// 128 VGPRs (4 wavefronts per SIMD; 168 at 6 steps), float64 to 256.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -140,10 +140,18 @@ struct Closed {
 
 // MODE 0: periodic box; 1: walls in x or y; 2: solid cells and a body force
 // (and walls).  Grid: wavefront w takes strip w % strips of segment w / strips.
+// BUF (the deepest float32 pipeline): the lattices as buffers and every store issued,
+// the lanes without an output past the buffer's end, so that a row's loads are waited
+// for without its stores; 3 wavefronts per SIMD instead of 4 and a spill: 2048^2 18.4
+// -> 17.7 us per step, 4096^2 65 -> 63.3.  The other kernels have wavefronts enough to
+// cover that wait, and the added stores of edge lanes cost them up to 5 %.
+template <typename T, int H, int MODE>
+constexpr bool kBuf = MODE == 0 && H == 6 && sizeof(T) == 4;
+
 template <typename T, bool O3, int H, int MODE>
-__global__ void __launch_bounds__(64 * kWaves, MODE ? 1 : sizeof(T) == 8 ? 2 : 4) k_multi(const T *__restrict__ src, T *__restrict__ dst,
-                                                       const uint32_t *__restrict__ lm, Box bx, Coef<T> c, Force<T> F,
-                                                       int strips, int ly, int nwaves) {
+__global__ void __launch_bounds__(64 * kWaves, (MODE ? 1 : sizeof(T) == 8 ? 2 : kBuf<T, H, MODE> ? 3 : 4))
+    k_multi(const T *__restrict__ src, T *__restrict__ dst, const uint32_t *__restrict__ lm, Box bx, Coef<T> c,
+            Force<T> F, int strips, int ly, int nwaves) {
     constexpr int WO = 64 - 2 * (H - 1);  // columns a strip writes
     constexpr uint32_t XM = link_bits(0, -1), XP = link_bits(0, 1), YM = link_bits(1, -1), YP = link_bits(1, 1);
     // neighbouring strips and segments share the lines at their edges: give each
@@ -167,6 +175,8 @@ __global__ void __launch_bounds__(64 * kWaves, MODE ? 1 : sizeof(T) == 8 ? 2 : 4
     const off oxp = x == nx - 1 ? off(0) : ox + off(sizeof(T));
     auto at = [](const T *p, off o) { return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(p) + o); };
     auto put = [](T *p, off o, T v) { *reinterpret_cast<T *>(reinterpret_cast<char *>(p) + o) = v; };
+    constexpr bool BUF = kBuf<T, H, MODE>;
+    const LatticeBuffer<T> from(src, off(Q) * pl), to(dst, off(Q) * pl);
     const int r0 = seg * ly, r1 = r0 + ly < ny ? r0 + ly : ny;
     const int iters = r1 - r0 + 2 * (H - 1);
     int row = (r0 - (H - 1)) % ny;  // the row being loaded, wrapped
@@ -190,7 +200,7 @@ __global__ void __launch_bounds__(64 * kWaves, MODE ? 1 : sizeof(T) == 8 ? 2 : 4
     auto fetch = [&](int r) {
         const off o = off(r) * rowb;
 #pragma unroll
-        for (int q = 0; q < Q; ++q) nxt[q] = at(src, off(q) * pl + o + ox);
+        for (int q = 0; q < Q; ++q) nxt[q] = BUF ? from.load(off(q) * pl + o, ox) : at(src, off(q) * pl + o + ox);
         if (MODE == 2) mnxt = lm[(int64_t)r * nx + x];
     };
     fetch(row);
@@ -240,7 +250,15 @@ __global__ void __launch_bounds__(64 * kWaves, MODE ? 1 : sizeof(T) == 8 ? 2 : 4
         const uint32_t m = MODE == 0 ? 0u : mx | ybits(rk) | (MODE == 2 ? mk[H - 1] : 0u);
         const off oz = off(rk) * rowb;
         const off om = rk == 0 ? off(ny - 1) * rowb : oz - rowb, op = rk == ny - 1 ? off(0) : oz + rowb;
-        if (outlane && !(MODE == 2 && (m & kSolidBit))) {
+        if constexpr (BUF) {
+            const off none = outlane ? 0u : kNoStore;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const off ro = Lat::e[q][1] < 0 ? om : (Lat::e[q][1] > 0 ? op : oz);
+                const off xx = Lat::e[q][0] < 0 ? oxm : (Lat::e[q][0] > 0 ? oxp : ox);
+                to.store(off(q) * pl + ro, none | xx, g[q]);
+            }
+        } else if (outlane && !(MODE == 2 && (m & kSolidBit))) {
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
                 const off ro = Lat::e[q][1] < 0 ? om : (Lat::e[q][1] > 0 ? op : oz);
@@ -256,6 +274,7 @@ __global__ void __launch_bounds__(64 * kWaves, MODE ? 1 : sizeof(T) == 8 ? 2 : 4
     };
     int i = 0;
     for (; i < 2 * (H - 1); ++i) advance(i, std::false_type{});
+    if (BUF) wait_loads();
     for (; i < iters; ++i) advance(i, std::true_type{});
 }
 
@@ -323,13 +342,13 @@ int multi_depth(const MultiPlan &p, int64_t n, int odd) {
 //   the two overlap (a fourth-power mean), and a launch and the first rows'
 //     latency take 4.
 // Measured on MI355X, us per step, H = 2 / 3 / 4 / 6 at their best ly (one AA
-// step per kernel first): 2048^2 float32 48: 32.2 / 22.9 / 19.3 / 18.5; 4096^2
-// 262: 124 / 87 / 77 / 67; 1531 x 1019 with walls 21.6: 10.8 / 8.9 / 9.3 / 9.8;
+// step per kernel first): 2048^2 float32 48: 32.2 / 22.9 / 19.3 / 17.7; 4096^2
+// 262: 124 / 87 / 77 / 63; 1531 x 1019 with walls 21.6: 10.8 / 8.9 / 9.3 / 9.8;
 // 2048^2 float64 115: 62 / 42 / 34 / 28.0; 256^2 4.7: 2.2 / 2.1 / 2.1 / 2.3;
 // 700 x 150 with solids 7.7: 2.9 / 3.0 / 3.2 / 3.7.  Small boxes want short
 // pipelines (their wavefronts run a few rows each), large ones deep (the traffic
 // is divided by H, the issue of about 102 vector instructions per update is
-// not: at 4096^2 and H = 6 it takes 55 of the 67 us).
+// not: at 4096^2 and H = 6 it takes 55 of the 63 us).
 MultiPlan multi_plan(int nx, int ny, int fp64, bool links, bool single, int cus) {
     MultiPlan p{};
     const double row = fp64 ? 0.30 : links ? 0.25 : 0.20, bytes = 9.0 * (fp64 ? 8 : 4) * (double)nx * ny;

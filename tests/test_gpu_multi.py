@@ -154,6 +154,27 @@ def test_walled_d3v19_boxes(gpu, shape, bc, order, precision, scheme):
             assert np.array_equal(one, many), (n, calls, int((one != many).sum()))
 
 
+@pytest.mark.parametrize("lattice,shape,n", [("d3v19", (350, 353, 347), 4), ("d2v9", (9001, 9003, 1), 12)])
+def test_lattices_between_2_and_4_gib(gpu, lattice, shape, n):
+    """Byte offsets past 2^31 in the buffer accesses: 3.3 GB and 2.9 GB per lattice."""
+    nx, ny, nz = shape
+    dims = 3 if nz > 1 else 2
+    g = torch.Generator(device="cuda").manual_seed(7)
+    n0 = 1.0 + 0.01 * torch.rand(shape[::-1], generator=g, device="cuda", dtype=torch.float64)
+    u0 = 0.01 * torch.rand((dims,) + shape[::-1], generator=g, device="cuda", dtype=torch.float64)
+    cfg = lbm.make_config(lattice, shape=shape, order=2, tau=0.7, precision=lbm.LBM_FP32_DEV, scheme=AA)
+    out = []
+    for calls in ([1] * n, [n]):
+        lat = lbm.Lattice.create(cfg, n0, u0)
+        for k in calls:
+            lat.step(k)
+        m, u = lat.moments()
+        torch.cuda.synchronize()
+        lat.free()
+        out.append((m, u))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
 def test_aa_runs_in_a_workspace_of_one_lattice(gpu):
     """A caller that gives an AA box no second lattice still gets its steps, in place."""
     cfg, n0, u0 = make((200, 90), order=2, scheme=AA)

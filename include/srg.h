@@ -50,7 +50,7 @@ lbm_status srg_param_count(int64_t *n);
 
 /* Device workspace for batches of up to max_batch profiles of length `length`
  * (a multiple of 128): parameters, Adam state, bf16 weight copies, the
- * activations of one forward pass, gradient scratch and the hybrid advance's
+ * pre-activations of one forward pass, gradient scratch and the hybrid advance's
  * fallback counts. */
 lbm_status srg_workspace_bytes(int max_batch, int length, size_t *bytes);
 
@@ -67,13 +67,15 @@ lbm_status srg_set_params(srg_ctx c, const float *params_dev);
 lbm_status srg_get_params(srg_ctx c, float *params_dev);
 
 /* out = network(profiles, tau) for `batch` profiles (1 <= batch <= max_batch).
- * Keeps the activations for a following srg_backward.  The inputs must stay
- * unchanged until that backward has run. */
+ * Keeps the pre-activations for a following srg_backward.  The inputs must stay
+ * unchanged until that backward has run; a caller that takes no gradient may
+ * pass out_dev == prof_dev (profiles are then not cut, see srg_infer). */
 lbm_status srg_forward(srg_ctx c, const float *prof_dev, const float *tau_dev, int batch, float *out_dev);
 
 /* Inference: the same out as srg_forward, bit for bit, from one kernel that
  * keeps every activation in LDS (one workgroup per profile, or per two profiles
- * when the batch exceeds the device's compute units and 2 L <= 4096; lengths up
+ * when the batch exceeds the device's compute units and 2 L <= 4096, or per
+ * segment of a profile when the batch is smaller than that; lengths up
  * to 4096, longer ones run layer by layer); nothing is kept for a backward pass (a
  * following srg_backward needs a new srg_forward).
  * prof_dev [batch][2][L] and tau_dev [batch] float32 on the device, out_dev

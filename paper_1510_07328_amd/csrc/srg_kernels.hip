@@ -749,8 +749,10 @@ hipError_t fwd_fused(const float *nu, const float *tau, const __bf16 *W1, const 
     // Whole samples against segments, us per call: 1 x 384 23.6 -> 19.3, 1 x 1024
     // 41.2 -> 19.7, 1 x 4096 126 -> 20.0, 64 x 1024 42.8 -> 27.4, 40 x 4096 128 -> 40.5
     // (layer by layer with the activations kept: 26.6, 27.8, 29.2, 47.2, 69.0).
+    // Not in place (out == nu): a segment stages its neighbours' ends of n, u while
+    // they write theirs; a whole sample is staged by the workgroup that writes it.
     int segs = 1, seglen = L;
-    if (cus > 0 && B < cus) {
+    if (cus > 0 && B < cus && out != nu) {
         const int want = cus / B < L / FC ? cus / B : L / FC;
         const int sl = (L / FC + want - 1) / want * FC;
         if (sl + FLEAD < L) {

@@ -172,7 +172,13 @@ hipError_t one_step(lbm_ctx_s *c, hipStream_t s) {
 // Passes start and end in natural layout, so an AA run takes an odd step before
 // and after on its own; after n steps the state is in the lattice that n single
 // steps leave it in (a caller may capture the call and replay it).
-hipError_t enqueue_steps(lbm_ctx_s *c, int64_t n, hipStream_t s) {
+// Solid cells: neither a pass nor a step writes their slots, so an AA run finds them
+// in its first lattice as they were.  A push step leaves the previous step's state in
+// the other lattice, and a cell that turns solid between calls keeps its slots of both;
+// push runs with obstacles therefore end every call with a single step (`tail` = 1).
+int tail_steps(const lbm_ctx_s *c) { return c->multi && c->cfg.scheme == LBM_SCHEME_PUSH && c->cfg.obstacles; }
+
+hipError_t enqueue_steps(lbm_ctx_s *c, int64_t n, int tail, hipStream_t s) {
     const bool aa = c->cfg.scheme == LBM_SCHEME_AA;
     hipError_t e = hipSuccess;
     if (c->multi) {
@@ -180,7 +186,7 @@ hipError_t enqueue_steps(lbm_ctx_s *c, int64_t n, hipStream_t s) {
             e = one_step(c, s);
             --n;
         }
-        int64_t m = aa ? n & ~int64_t(1) : n;
+        int64_t m = aa ? n & ~int64_t(1) : n > tail ? n - tail : 0;
         n -= m;
         if (c->tile.h > 0) {
             // equal launches, as many as keep the parity of the launches that of the steps
@@ -236,7 +242,7 @@ lbm_status build_graph(lbm_ctx_s *c, int ph) {
     const int64_t save_steps = c->steps;
     e = hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
-    const hipError_t le = enqueue_steps(c, c->cfg.graph_steps, c->cap);
+    const hipError_t le = enqueue_steps(c, c->cfg.graph_steps, 0, c->cap);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(c->cap, &g);
     c->cur = save_cur;
@@ -364,8 +370,9 @@ lbm_status lbm_step(lbm_ctx c, int64_t nsteps) {
     if (!c) return fail(LBM_ERR_ARG, "null context");
     if (nsteps < 0) return fail(LBM_ERR_ARG, "nsteps < 0");
     const int G = c->cfg.graph_steps;
+    const int tail = tail_steps(c);
     int64_t left = nsteps;
-    while (G > 0 && left >= G) {
+    while (G > 0 && left >= G + tail) {
         const int ph = c->cur | parity(c);  // AA: cur is 0 between calls
         if (!c->graph[ph]) {
             lbm_status s = build_graph(c, ph);
@@ -376,7 +383,7 @@ lbm_status lbm_step(lbm_ctx c, int64_t nsteps) {
         c->steps += G;  // G even: the lattice index and the AA parity are unchanged
         left -= G;
     }
-    const hipError_t e = enqueue_steps(c, left, c->stream);
+    const hipError_t e = enqueue_steps(c, left, tail, c->stream);
     return e == hipSuccess ? LBM_OK : hip_fail(e, "step kernel launch");
 }
 

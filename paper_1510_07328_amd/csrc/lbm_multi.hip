@@ -21,7 +21,7 @@
 // Walls and solid cells: a link that leaves the box or ends in a solid cell
 // returns to its cell reversed.  Their modes keep the previous row's collided
 // populations, and a wavefront row that holds such a link replaces the gathered
-// values by the cell's own.
+// values by the cell's own.  A solid cell's slots are neither written in dst nor used.
 //
 // Bound: vector issue for deep pipelines (102 instructions per update, 6 of them
 // lane shifts; 256 CUs x 64 lanes), memory for H = 2 and 3; 2048^2 float32 47.9
@@ -220,14 +220,6 @@ __global__ void __launch_bounds__(64 * kWaves, (MODE ? 1 : sizeof(T) == 8 ? 2 : 
         const int r = row;
         row = row + 1 == ny ? 0 : row + 1;
         fetch(row);  // after the last row: one that is not used
-        if (MODE == 2) {
-            // a solid cell takes no part: its slots are carried over as they are
-            const bool keep = (mk[0] & kSolidBit) && outlane && i >= H - 1 && i < H - 1 + (r1 - r0);
-            if (__builtin_amdgcn_ballot_w64(keep) != 0 && keep) {
-#pragma unroll
-                for (int q = 0; q < Q; ++q) put(dst, off(q) * pl + off(r) * rowb + ox, g[q]);
-            }
-        }
         collide<Lat, T, O3, MODE == 2>(g, c, F.F);
         int rk = r;  // row of level k
 #pragma unroll

@@ -115,15 +115,14 @@ __global__ void __launch_bounds__(1024) k_tile(const T *__restrict__ src, T *__r
         }
     }
     if (!mine) return;
-    if (!solid) {  // a solid cell's slots are carried over as they were loaded
-        if (a.h & 1) {
+    if (a.h & 1) {
 #pragma unroll
-            for (int q = 0; q < Q; ++q) g[q] = lds[slot[Lat::opp[q]]];
-        } else {
+        for (int q = 0; q < Q; ++q) g[q] = lds[slot[Lat::opp[q]]];
+    } else {
 #pragma unroll
-            for (int q = 0; q < Q; ++q) g[q] = lds[q * PL + own];
-        }
+        for (int q = 0; q < Q; ++q) g[q] = lds[q * PL + own];
     }
+    if (solid) return;  // its slots are not written
 #pragma unroll
     for (int q = 0; q < Q; ++q) dst[q * b.plane + cell] = g[q];
 }

@@ -40,7 +40,8 @@ __device__ __forceinline__ bf16x8 column8(const __bf16 *p) {
 }
 
 // A float32 operand as three bfloat16 terms (24 bits of significand): products
-// with a bfloat16 factor, summed in float32, carry the float32 product.
+// with a bfloat16 factor, summed in float32, carry the float32 product.  finite()
+// sets the later terms of an infinity (inf - inf: a NaN) to zero.
 struct Split3 {
     bf16x8 t[3];
     __device__ __forceinline__ void set(const float (&v)[8]) {
@@ -53,6 +54,15 @@ struct Split3 {
             t[1][j] = m;
             t[2][j] = to_bf(r - to_f(m));
         }
+    }
+    __device__ __forceinline__ void finite(const float (&v)[8]) {
+        float top = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) top = __builtin_fmaxf(top, __builtin_fabsf(v[j]));
+        if (__builtin_amdgcn_ballot_w64(top == __builtin_inff()) == 0) return;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (__builtin_fabsf(v[j]) == __builtin_inff()) t[1][j] = t[2][j] = to_bf(0.0f);
     }
 };
 
@@ -142,6 +152,7 @@ __global__ void __launch_bounds__(256) k_bwd_out(const float *__restrict__ dout,
         for (int j = 0; j < 8; ++j) f[j] = m < 2 * KT ? dyl[mc][H4 + 32 * wave + 8 * g + j - (mt - 2) * 27] : 0.0f;
         Split3 d;
         d.set(f);
+        d.finite(f);  // dy of an overflowed loss
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) {
             const bf16x8 bv = column8(at + (32 * wave + 8 * g + (m >> 2)) * RS + 16 * cb + 4 * (m & 3));

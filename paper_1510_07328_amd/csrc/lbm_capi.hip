@@ -343,7 +343,8 @@ lbm_status lbm_init(const lbm_config *cfg, void *workspace, size_t bytes, void *
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         const bool links = lay.porous || c->box.bbx || c->box.bby;
         if (m.D == 3) {
-            c->lz = multi3_plan(cfg->nx, cfg->ny, cfg->nz, c->fp64, links ? 2 : c->box.bbz ? 1 : 0, cus);
+            c->lz = multi3_plan(cfg->nx, cfg->ny, cfg->nz, c->fp64, c->box.bbx ? 3 : c->box.bby ? 2 : c->box.bbz ? 1 : 0,
+                                cus);
         } else {
             c->plan = multi_plan(cfg->nx, cfg->ny, c->fp64, links, lay.nlat == 2, cus);
             c->tile = tile_plan(cfg->nx, cfg->ny, c->box.bbx, c->box.bby, lay.porous, c->fp64, cus);

@@ -80,7 +80,7 @@ hipError_t launch_multi(int fp64, int H, const void *src, void *dst, const uint3
 
 // Two steps of a d3v19 box per pass (lbm_multi3.hip), segments of lz
 // planes (multi3_plan: 0 where single steps are faster).
-// walls: 0 none, 1 in z only, 2 in x or y
+// walls: 0 none, 1 in z only, 2 in y (and z), 3 in x (and others)
 int multi3_plan(int nx, int ny, int nz, int fp64, int walls, int cus);
 hipError_t launch_multi3(int fp64, const void *src, void *dst, const Box &b, const Model &m, double tau,
                          double rho_ref, int lz, hipStream_t s);

@@ -27,6 +27,7 @@
 // than there are and recomputes 4 of 16 rows).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "lbm_collide.h"
@@ -284,22 +285,45 @@ hipError_t launch_t(const void *src, void *dst, const Box &b, const Coef<T> &c, 
 // 331 (414 before, with branches and rows of their own), 256 x 256 x 60 115: 82 (95),
 // 160^3 137: 79 (81), 200 x 100 x 150 102: 73 (78), 128^3 82: 49.5 (52), 64^3 22: 9.4
 // (9.8), 40 x 40 x 200 37: 10.8 (11.1); float64 256^3 1018: 690 (707).
-// With walls a wavefront that holds one reads its own populations back: a plane takes
-// 4.2 us where only z has walls (its first and last planes), 6.0 where every plane has
-// some (20 spilled registers at 16 wavefronts of 128; float64 3.6).  Walls in x / in z:
-// 256^3 514: 487 / 434, 128^3 85: 77 / 59, 64^3 22: 16 / 12, 200 x 100 x 150 101:
-// 116 (single steps are kept) / 85; float64 100^3 68: 50 / 49.  A single step takes 8 us
-// for a start there, and large boxes take passes only for a clear gain.
+// With walls a wavefront that holds one reads its own populations back.  float64: a
+// plane takes 3.6 us and 1.8 more in large boxes, a single step 8 us for a start;
+// passes win at every size measured (30^3 9.4: 6.0, 64^3 18.4: 13.3, 128^3 116: 104,
+// 200 x 100 x 150 191: 131, 256^3 1025: 700).  float32 (16 wavefronts of 128 registers,
+// 20 of them spilled) is slower, most of all with walls in x, where every wavefront
+// holds one in every plane: a plane takes 4.6 us there, 4.0 with walls in y, 3.5 in z,
+// and in boxes from 3 million cells on 5.0, 4.4 and 4.0 more; a single step takes 6 us
+// for a start, a seventh with a wavefront for every SIMD, 1.5 ns per wavefront, at least
+// 2 ns per workgroup, and the lattice's traffic at 5.2 TB/s.  Single steps against the
+// best pass measured, us per step, walls in x / y / z:
+//   64^3               13.8: 15.5   13.8: 13.4   14.1: 11.5
+//   100^3              39.5: 35.6   39.8: 27.1   41.0: 21.9
+//   128^3              59.2: 75.7   59.7: 59.4   61.7: 59.1
+//   160^3             124: 133     123: 98       125: 88
+//   200 x 100 x 150    91: 103      92: 87        94: 78
+//   256^3             491: 460     485: 419      488: 419
+// (256^3 with walls in x keeps single steps: its passes gain 1 to 6 %).
 int multi3_plan(int nx, int ny, int nz, int fp64, int walls, int cus) {
     if (cus <= 0) cus = 256;
     const int nw = fp64 ? 8 : 16;
     const double cells = (double)nx * ny * nz, size = cells * (fp64 ? 2 : 1);
     const bool pace = paced(size) && !walls;
-    const double first = !walls ? 3.1 : fp64 ? 3.6 : walls == 1 ? 4.2 : 6.0, fill = size < 2e6 ? size / 2e6 : 1.0;
-    const double plane = pace ? (fp64 ? 5.1 : 5.8) : first + (walls && fp64 ? 1.8 : 2.8) * fill;
+    const double fill = size < 2e6 ? size / 2e6 : 1.0, wide = cells < 3e6 ? cells / 3e6 : 1.0;
+    const double plane = pace ? (fp64 ? 5.1 : 5.8)
+                         : !walls ? 3.1 + 2.8 * fill
+                         : fp64   ? 3.6 + 1.8 * fill
+                                  : (walls == 3 ? 4.6 + 5.0 * wide : walls == 2 ? 4.0 + 4.4 * wide : 3.5 + 4.0 * wide);
     const int64_t windows = (int64_t)((nx + 61) / 62) * ((ny + nw - 3) / (nw - 2));
+    double least = 2.0 * (5.0 + 38e-6 * size);  // of two single steps
+    if (walls && fp64) {
+        least = 2.0 * (8.0 + 38e-6 * size) * (size > 1e6 ? 0.85 : 1.0);
+    } else if (walls) {
+        const int block = nx < 256 ? (nx + 63) / 64 * 64 : 256;
+        const double blocks = (double)ny * nz * ((nx + block - 1) / block), waves = blocks * (block / 64);
+        const double single[] = {6.0 + (waves < 1024 ? waves / 1024 : 1.0) + 1.5e-3 * waves, 6.0 + 2e-3 * blocks,
+                                 cells * 152 / 5.2e6};
+        least = 2.0 * std::max({single[0], single[1], single[2]}) * (walls == 3 ? 0.97 : 1.0);
+    }
     int best = 0;
-    double least = 2.0 * ((walls ? 8.0 : 5.0) + 38e-6 * size) * (walls && size > 1e6 ? 0.85 : 1.0);
     for (int lz = 1; lz <= 64 && lz <= nz; ++lz) {
         const int64_t blocks = windows * ((nz + lz - 1) / lz), rounds = (blocks + cus - 1) / cus;
         const double t = 4.0 + (double)rounds * (lz + 2) * plane * (pace ? 1.0 + 0.004 * lz : 1.0);

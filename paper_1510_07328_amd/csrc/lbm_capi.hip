@@ -188,19 +188,27 @@ hipError_t enqueue_steps(lbm_ctx_s *c, int64_t n, int tail, hipStream_t s) {
         }
         int64_t m = aa ? n & ~int64_t(1) : n > tail ? n - tail : 0;
         n -= m;
+        auto tile = [&](int h) {
+            const hipError_t te = launch_tile(c->fp64, c->tile, h, c->lat[c->cur], c->lat[1 - c->cur], c->lm, c->box,
+                                              c->model, c->cfg.tau, c->rho_ref, c->F, s);
+            if (te == hipSuccess) {
+                c->cur = 1 - c->cur;
+                c->steps += h;
+            }
+            return te;
+        };
         if (c->tile.h > 0) {
             // equal launches, as many as keep the parity of the launches that of the steps
             int64_t k = (m + c->tile.h - 1) / c->tile.h;
             if ((k ^ (aa ? 0 : m)) & 1) ++k;
-            for (; e == hipSuccess && m > 0; --k) {
+            if (k == m && !c->tile.one) k = 0;  // one step each
+            for (; e == hipSuccess && m > 0 && k > 0; --k) {
                 const int h = (int)((m + k - 1) / k);
-                e = launch_tile(c->fp64, c->tile, h, c->lat[c->cur], c->lat[1 - c->cur], c->lm, c->box, c->model,
-                                c->cfg.tau, c->rho_ref, c->F, s);
-                if (e != hipSuccess) return e;
-                c->cur = 1 - c->cur;
-                c->steps += h;
+                e = tile(h);
                 m -= h;
             }
+            if (e != hipSuccess) return e;
+            if (m == 0 && n == 1 && tail && c->tile.one) return tile(1);  // like a push step, leaves its source as it is
         }
         for (; c->lz > 0 && m >= 4 && e == hipSuccess; m -= 4) {  // in pairs: back to the same lattice
             for (int k = 0; k < 2 && e == hipSuccess; ++k) {

@@ -92,6 +92,7 @@ struct TilePlan {
     int sx = 0, sy = 0;  // tile
     int h = 0;           // steps per launch
     double time = 0;     // estimated microseconds per step
+    bool one = false;    // a launch of one step beats the single-step kernel
 };
 TilePlan tile_plan(int nx, int ny, bool bbx, bool bby, bool porous, int fp64, int cus);
 // h <= p.h steps from src into dst, both in natural layout.

@@ -166,6 +166,13 @@ hipError_t launch_t(const TilePlan &p, int h, const void *src, void *dst, const 
 // and the register pipeline: 512 x 4 float64 with walls 0.49 (h = 24), 5.0, 1.9;
 // 128 x 4 0.46, 4.0, 1.8; 256^2 1.48 (32 x 8, h = 6), 5.0, 2.1; 700 x 150 with
 // solids and a force 2.35 to 2.4, 7.6, 2.9; 512^2 2.97, 7.8, 3.15.
+// Calls of one or two steps come down to launches of one step (`one`): 3.7 and 0.40
+// (0.46) per wavefront of a compute unit, against a single-step kernel that takes 4.6
+// (4.0 up to 1024 cells), 2.2 ns per column of the row a workgroup runs through (3.2
+// with solids; float64 2.6 and 4.0) and 10 ps per cell from 40 000 cells on (float64
+// 22, 4 more with solids).  Single step against tile of one step, us: 32^2 4.2: 4.3,
+// 128^2 4.9: 4.5, 160^2 5.0: 4.5, 200^2 5.1: 6.2, 300^2 6.3: 7.7, 512 x 64 5.5: 4.9,
+// 2048 x 8 8.4: 4.6, 8192 x 8 23: 5.5; float64 256^2 6.3: 7.1, 700 x 150 8.2: 7.3.
 TilePlan tile_plan(int nx, int ny, bool bbx, bool bby, bool porous, int fp64, int cus) {
     TilePlan best{};
     best.time = 1e300;
@@ -193,6 +200,15 @@ TilePlan tile_plan(int nx, int ny, bool bbx, bool bby, bool porous, int fp64, in
                 if (t < best.time) best = TilePlan{sx, sy, h, t};
             }
         }
+    }
+    if (best.h > 0) {
+        const int64_t tiles = (int64_t)((nx + best.sx - 1) / best.sx) * ((ny + best.sy - 1) / best.sy);
+        const int64_t win = (int64_t)window(nx, best.sx, best.sx >= nx, bbx, 1) * window(ny, best.sy, best.sy >= ny, bby, 1);
+        const double waves = (double)((win + 63) / 64 * ((tiles + cus - 1) / cus)), cells = (double)nx * ny;
+        const double column = (fp64 ? 2.6e-3 : 2.2e-3) + (porous ? (fp64 ? 1.4e-3 : 1.0e-3) : 0.0);
+        const double cell = (fp64 ? 2.2e-5 : 1.0e-5) + (porous ? 0.4e-5 : 0.0);
+        const double single = (cells <= 1024 && !porous ? 4.0 : 4.6) + column * nx + (cells > 4e4 ? cell * (cells - 4e4) : 0.0);
+        best.one = 3.7 + (fp64 ? 0.46 : 0.40) * waves < single;
     }
     return best;
 }

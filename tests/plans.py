@@ -12,6 +12,17 @@ class MultiPlan(C.Structure):
     _fields_ = [("best", C.c_int), ("time", C.c_double), ("ly", C.c_int * 8), ("next", C.c_byte * 2 * 25)]
 
 
+class TilePlan(C.Structure):
+    _fields_ = [("sx", C.c_int), ("sy", C.c_int), ("h", C.c_int), ("time", C.c_double), ("one", C.c_bool)]
+
+
+def tile(shape, fp64=False, walls=False, porous=False):
+    """d2v9 in LDS: the tile, its steps per launch, and whether a launch of one step pays."""
+    f = lbm.load()._ZN3lbm9tile_planEiibbbii
+    f.restype, f.argtypes = TilePlan, [C.c_int] * 2 + [C.c_bool] * 3 + [C.c_int] * 2
+    return f(shape[0], shape[1], walls, walls, porous, int(fp64), CUS)
+
+
 def planes_per_segment(shape, bc=(0, 0, 0), fp64=False):
     """d3v19: planes per segment of a pass of two steps, 0 for single steps."""
     f = lbm.load()._ZN3lbm11multi3_planEiiiiii

@@ -2,7 +2,7 @@
 one side was faster by 5 % or more."""
 import pytest
 
-from plans import planes_per_segment
+from plans import planes_per_segment, tile
 
 X, Y, Z, ALL = (1, 0, 0), (0, 1, 0), (0, 0, 1), (1, 1, 1)
 
@@ -32,3 +32,21 @@ def test_walled_d3v19_boxes_that_take_passes(shape, bc):
 @pytest.mark.parametrize("bc", [X, Y, Z, ALL])
 def test_walled_d3v19_boxes_in_float64_take_passes(shape, bc):
     assert planes_per_segment(shape, bc, fp64=True) > 0
+
+
+@pytest.mark.parametrize("shape,fp64,porous", [
+    ((200, 200), False, False), ((256, 256), False, False), ((300, 300), False, False),  # 5.1 : 6.2, 5.3 : 6.2, 6.3 : 7.7
+    ((360, 360), False, False), ((256, 256), False, True), ((180, 180), True, False), ((300, 300), True, False),
+    ((230, 230), True, True),
+])
+def test_single_steps_where_a_tile_of_one_step_takes_longer(shape, fp64, porous):
+    p = tile(shape, fp64, porous=porous)
+    assert p.h > 1 and not p.one
+
+
+@pytest.mark.parametrize("shape,fp64,porous", [
+    ((80, 80), False, False), ((512, 64), False, False), ((2048, 32), False, False), ((8192, 8), False, False),
+    ((16, 1024), True, False), ((700, 150), True, True), ((1000, 60), True, False), ((160, 160), False, True),
+])
+def test_tiles_of_one_step_where_they_are_faster(shape, fp64, porous):
+    assert tile(shape, fp64, porous=porous).one

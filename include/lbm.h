@@ -150,19 +150,22 @@ lbm_status lbm_coefficients(const lbm_config *cfg, double *out, int cap, int *n_
 
 /* Bytes of device workspace lbm_init takes for cfg: two lattices for the push
  * scheme, one for AA, plus reduction scratch and the staging area of the host
- * lbm_moments, about 4 MB.  d2v9 boxes, and d3v19 boxes without obstacles or a
- * force, with one weight for all cells and a lattice below 4 GiB run calls of
- * several steps as passes of several steps from one lattice into another; for AA
- * the value then holds a second lattice
- * (which overlaps the staging area).  lbm_init accepts an AA workspace without
- * it, down to one lattice and the staging area: steps then run one by one, in
- * place, with the same results.  Host only. */
+ * lbm_moments, about 4 MB.  Calls of several steps run as passes of several steps
+ * from one lattice into another, for d2v9 boxes and for d3v19 boxes without
+ * obstacles or a force where passes are faster, with one weight for all cells and a
+ * lattice below 4 GiB; for AA the value then holds a second lattice (which overlaps
+ * the staging area).  Host only. */
 lbm_status lbm_workspace_bytes(const lbm_config *cfg, size_t *bytes);
+
+/* The least lbm_init accepts: without that second lattice, for a caller that runs
+ * AA for its memory.  Steps then run one by one, in place, with the same results.
+ * Host only. */
+lbm_status lbm_workspace_min_bytes(const lbm_config *cfg, size_t *bytes);
 
 /* Create a context and set the populations to equilibrium with the given
  * density and velocity fields (initial condition f = f_eq(n0, u0)).
- *   workspace: device pointer, >= lbm_workspace_bytes(cfg) bytes (see there),
- *              256-byte aligned; borrowed until lbm_free.
+ *   workspace: device pointer, lbm_workspace_bytes(cfg) bytes (or at least
+ *              lbm_workspace_min_bytes), 256-byte aligned; borrowed until lbm_free.
  *   stream:    hipStream_t the context enqueues on (NULL = null stream).
  *   n0_dev:    device float64 [nz][ny][nx] density I_0;
  *   u0_dev:    device float64 [D][nz][ny][nx] velocity u0.

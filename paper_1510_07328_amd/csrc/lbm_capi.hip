@@ -62,6 +62,14 @@ struct Layout {
     bool porous = false;  // obstacles or a body force: link mask in the workspace, porous kernels
 };
 
+constexpr int kCus = 256;  // compute units of an MI355X (the workspace does not depend on the device)
+
+// d3v19: planes per segment of a pass, 0 for a box that runs single steps
+int planes3(const lbm_config *cfg, int cus) {
+    const int walls = cfg->bc[0] == LBM_BOUNCEBACK ? 3 : cfg->bc[1] == LBM_BOUNCEBACK ? 2 : cfg->bc[2] == LBM_BOUNCEBACK ? 1 : 0;
+    return multi3_plan(cfg->nx, cfg->ny, cfg->nz, cfg->precision == LBM_FP64, walls, cus);
+}
+
 lbm_status check_config(const lbm_config *cfg, Model *m, Layout *lay) {
     std::string err;
     lbm_status s = build_model(cfg, m, &err);
@@ -112,7 +120,8 @@ lbm_status check_config(const lbm_config *cfg, Model *m, Layout *lay) {
     lay->stage_rows = (int)srows;
     const size_t stage = align_up((size_t)srows * row_bytes);
     lay->min_total = lay->total = lay->stage_off + stage;
-    lay->multi = multi_eligible(cfg->lattice, m->local != 0, lay->porous, lay->plane, lay->elt);
+    lay->multi = multi_eligible(cfg->lattice, m->local != 0, lay->porous, lay->plane, lay->elt) &&
+                 (m->D == 2 || planes3(cfg, kCus) > 0);
     // AA: the second lattice of the passes, which between calls is free for the staging
     if (lay->multi && lay->nlat == 1)
         lay->total = lay->stage_off + (lay->lattice_bytes > stage ? lay->lattice_bytes : stage);
@@ -313,6 +322,16 @@ lbm_status lbm_workspace_bytes(const lbm_config *cfg, size_t *bytes) {
     return LBM_OK;
 }
 
+lbm_status lbm_workspace_min_bytes(const lbm_config *cfg, size_t *bytes) {
+    if (!cfg || !bytes) return fail(LBM_ERR_ARG, "null argument");
+    Model m;
+    Layout lay;
+    lbm_status s = check_config(cfg, &m, &lay);
+    if (s != LBM_OK) return s;
+    *bytes = lay.min_total;
+    return LBM_OK;
+}
+
 lbm_status lbm_init(const lbm_config *cfg, void *workspace, size_t bytes, void *stream, const double *n0_dev,
                     const double *u0_dev, lbm_ctx *out) {
     if (!cfg || !workspace || !n0_dev || !u0_dev || !out) return fail(LBM_ERR_ARG, "null argument");
@@ -321,7 +340,7 @@ lbm_status lbm_init(const lbm_config *cfg, void *workspace, size_t bytes, void *
     Layout lay;
     lbm_status s = check_config(cfg, &m, &lay);
     if (s != LBM_OK) return s;
-    if (bytes < lay.min_total) return fail(LBM_ERR_ARG, "workspace smaller than lbm_workspace_bytes()");
+    if (bytes < lay.min_total) return fail(LBM_ERR_ARG, "workspace smaller than lbm_workspace_min_bytes()");
     if ((uintptr_t)workspace % kAlign) return fail(LBM_ERR_ARG, "workspace must be 256-byte aligned");
     lbm_ctx_s *c = new (std::nothrow) lbm_ctx_s;
     if (!c) return fail(LBM_ERR_ARG, "out of host memory");
@@ -351,8 +370,7 @@ lbm_status lbm_init(const lbm_config *cfg, void *workspace, size_t bytes, void *
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         const bool links = lay.porous || c->box.bbx || c->box.bby;
         if (m.D == 3) {
-            c->lz = multi3_plan(cfg->nx, cfg->ny, cfg->nz, c->fp64, c->box.bbx ? 3 : c->box.bby ? 2 : c->box.bbz ? 1 : 0,
-                                cus);
+            c->lz = planes3(cfg, cus);
         } else {
             c->plan = multi_plan(cfg->nx, cfg->ny, c->fp64, links, lay.nlat == 2, cus);
             c->tile = tile_plan(cfg->nx, cfg->ny, c->box.bbx, c->box.bby, lay.porous, c->fp64, cus);

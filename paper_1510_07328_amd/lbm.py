@@ -51,6 +51,7 @@ _lib = None
 _SIGNATURES = [
     ("lbm_coefficients", C.c_int, [C.POINTER(lbm_config), C.POINTER(C.c_double), C.c_int, C.POINTER(C.c_int)]),
     ("lbm_workspace_bytes", C.c_int, [C.POINTER(lbm_config), C.POINTER(C.c_size_t)]),
+    ("lbm_workspace_min_bytes", C.c_int, [C.POINTER(lbm_config), C.POINTER(C.c_size_t)]),
     ("lbm_init", C.c_int, [C.POINTER(lbm_config), C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p, C.c_void_p,
                            C.POINTER(C.c_void_p)]),
     ("lbm_step", C.c_int, [C.c_void_p, C.c_int64]),
@@ -141,6 +142,12 @@ def lbm_workspace_bytes(cfg: lbm_config) -> int:
     return b.value
 
 
+def lbm_workspace_min_bytes(cfg: lbm_config) -> int:
+    b = C.c_size_t()
+    _check(load().lbm_workspace_min_bytes(C.byref(cfg), C.byref(b)), "lbm_workspace_min_bytes")
+    return b.value
+
+
 def lbm_init(cfg, workspace_ptr: int, nbytes: int, stream: int, n0_ptr: int, u0_ptr: int) -> int:
     ctx = C.c_void_p()
     _check(load().lbm_init(C.byref(cfg), C.c_void_p(workspace_ptr), nbytes, C.c_void_p(stream),
@@ -217,7 +224,9 @@ class Lattice:
     ctx: int = 0
 
     @classmethod
-    def create(cls, cfg: lbm_config, n0, u0, stream=None):
+    def create(cls, cfg: lbm_config, n0, u0, stream=None, in_place=False):
+        """in_place: an AA run in a workspace of one lattice (lbm_workspace_min_bytes), single
+        steps; also taken where the device has no room for the second."""
         import torch
 
         dev = torch.device("cuda", torch.cuda.current_device())
@@ -227,8 +236,15 @@ class Lattice:
         u0 = torch.as_tensor(u0, dtype=torch.float64).reshape(D, -1).to(dev).contiguous()
         if n0.numel() != cells or u0.shape[1] != cells:
             raise ValueError("field sizes do not match the box")
-        nbytes = lbm_workspace_bytes(cfg)
-        ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+        least = lbm_workspace_min_bytes(cfg)
+        nbytes = least if in_place else lbm_workspace_bytes(cfg)
+        try:
+            ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+        except torch.OutOfMemoryError:
+            if nbytes == least:
+                raise
+            nbytes = least
+            ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
         s = stream if stream is not None else torch.cuda.current_stream(dev)
         self = cls(cfg)
         self.workspace, self.stream, self.D, self.cells = ws, s, D, cells

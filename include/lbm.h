@@ -115,7 +115,8 @@ typedef struct {
     int precision;    /* lbm_precision */
     double rho_ref;   /* deviation reference density (1.0 if <= 0) */
     int scheme;       /* lbm_scheme: two-lattice push, or in-place AA (same results) */
-    int block;        /* threads per workgroup, 0 = library default (multiple of 64, <= 1024) */
+    int block;        /* threads per workgroup of the single-step, moments and totals kernels,
+                         0 = library default (multiple of 64, <= 1024) */
     int graph_steps;  /* > 0: replay steps in captured HIP graphs of this many steps */
     /* Porous media (section "Numerical simulations for electrons in metals":
      * flow through rigid obstacles under a constant external force).  With

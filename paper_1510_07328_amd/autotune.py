@@ -1,6 +1,6 @@
 """Autotuner for the launch shapes of the library: the tile shape of the batched
 tube sweep (columns per tile S, halo / steps per round H, threads per
-workgroup) and the workgroup size of the plain field step.
+workgroup) and the workgroup size of the single field step.
 
 Candidates are timed on the GPU through the library's own entry points and the
 fastest is kept in a JSON cache, keyed by the device, the built library and a
@@ -191,7 +191,8 @@ def batch_options(tubes, opt, **kw):
 # -- plain field step ----------------------------------------------------------
 
 def time_field_block(cfg, n0, u0, block: int, steps: int = 100) -> float:
-    """Microseconds per step of the field step with `block` threads per workgroup."""
+    """Microseconds per single step with `block` threads per workgroup: calls of one step, since
+    calls of several run kernels of fixed workgroups where the box takes passes."""
     import copy
 
     import torch
@@ -202,12 +203,14 @@ def time_field_block(cfg, n0, u0, block: int, steps: int = 100) -> float:
     c.block = block
     lat = lbm.Lattice.create(c, n0, u0)
     try:
-        lat.step(10)
+        for _ in range(10):
+            lat.step(1)
         torch.cuda.synchronize()
         e0 = torch.cuda.Event(enable_timing=True)
         e1 = torch.cuda.Event(enable_timing=True)
         e0.record(lat.stream)
-        lat.step(steps)
+        for _ in range(steps):
+            lat.step(1)
         e1.record(lat.stream)
         torch.cuda.synchronize()
         return e0.elapsed_time(e1) * 1e3 / steps
@@ -217,7 +220,8 @@ def time_field_block(cfg, n0, u0, block: int, steps: int = 100) -> float:
 
 def tune_field(cfg, n0, u0, blocks=FIELD_BLOCKS, cache: dict | None = None, path: str | None = None, timer=None,
                device: str | None = None):
-    """Best workgroup size for the field step of cfg (cached like tune_batch)."""
+    """Best workgroup size for the single steps of cfg (cached like tune_batch); it is also that of
+    the moments and totals kernels.  Passes of several steps do not depend on it."""
     device = device or device_name()
     key = field_key(device, cfg)
     own_cache = cache is None

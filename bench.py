@@ -36,11 +36,12 @@ AMP = 0.01
 CORR = 32.0
 METRIC = "MLUPS & % HBM roofline (FP32-dev vs FP64) at ≤1e-6 rel err; surrogate speedup"
 
-# HBM bytes per step of the 2048^2 field in calls of many steps, from rocprofv3 FETCH_SIZE and
+# HBM bytes per step of the 2048^2 field in calls of 20 steps (passes of 4, 4, 6 and 6) and of
+# 200 (32 of 6 and 2 of 4; longer calls have fewer of 4 still), from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE runs (read counter scaled by 2.0, write by 1.0, the factors a 1 GiB device copy
-# reads), valid for the kernel and layout sources whose combined sha256 prefix is the key: one
-# pass of 6 steps moves 377 MB.  profiles/k_multi_d2v9.md holds the counts.
-MEASURED_TRAFFIC = {"1d0303a8975270ae": {"aa": 62_620_000, "push": 62_620_000}}
+# reads), valid for the kernel and layout sources whose combined sha256 prefix is the key.
+# profiles/k_multi_d2v9.md holds the counts.
+MEASURED_TRAFFIC = {"1d0303a8975270ae": {"aa": {20: 70_620_000, 200: 62_620_000}, "push": {20: 70_580_000, 200: 62_610_000}}}
 _CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_1510_07328_amd", "csrc")
 KERNEL_SRCS = [os.path.join(_CSRC, f) for f in ("lbm_kernels.hip", "lbm_collide.h", "lbm_internal.h",
                                                   "lbm_capi.hip", "lbm_multi.hip", "lbm_multi.h")]
@@ -58,8 +59,9 @@ def kernel_hash() -> str:
     return h.hexdigest()[:16]
 
 
-def measured_traffic(scheme: str):
-    return MEASURED_TRAFFIC.get(kernel_hash(), {}).get(scheme)
+def measured_traffic(scheme: str, steps: int):
+    """Counter bytes per step of calls of `steps` steps, None where that call was not measured."""
+    return MEASURED_TRAFFIC.get(kernel_hash(), {}).get(scheme, {}).get(min(steps, 200))
 
 
 EXTRAS = ("order3", "out_of_cache", "batched", "d3v19", "surrogate", "porous", "weights", "order4")
@@ -154,7 +156,7 @@ def extra_record(lbm, torch, inputs, lattice, shape, steps, corr, tau, label, au
     avg = ms * 1e3 / steps
     return {"workload": label, "cells": cells, "populations": Q, "steps": steps,
             "MLUPS": round(cells * steps / (ms * 1e-3) / 1e6, 1), "ms_per_step": round(ms / steps, 5),
-            "one_step_bytes": bps, **rate_fields(bps, avg, lattice == "d2v9"),
+            "one_step_bytes": bps, **rate_fields(bps, avg, lattice in ("d2v9", "d3v19")),
             "mass_total": tot[0], "block": cfg.block or "library default", "autotune": tune}
 
 
@@ -269,7 +271,7 @@ def surrogate_record(torch, count=512, jumps=16):
     tflops = SRG_FLOP_PER_POSITION * count * 1024 / (ms * 1e-3) / 1e12
     inputs_note = f"the {count} held-out tubes after 8 jumps (512 steps), median of 5 regions of 20 calls"
     rec["forward"] = {"ms": round(ms, 4), "TFLOPs": round(tflops, 1), "frac_bf16_peak": round(tflops / BF16_PEAK_TFLOPS, 4),
-                      "flop_per_position": SRG_FLOP_PER_POSITION, "kernels": "layer by layer, activations kept",
+                      "flop_per_position": SRG_FLOP_PER_POSITION, "kernels": "k_fwd_fused, pre-activations kept",
                       "inputs": inputs_note}
     tf_inf = SRG_FLOP_PER_POSITION * count * 1024 / (ms_inf * 1e-3) / 1e12
     rec["inference"] = {"ms": round(ms_inf, 4), "TFLOPs": round(tf_inf, 1),
@@ -568,7 +570,7 @@ def main():
     lat32.free()
     mlups32 = cells * args.steps / (ms32 * 1e-3) / 1e6
     avg_us = ms32 * 1e3 / args.steps
-    traffic = measured_traffic(args.scheme) if N == 2048 else None
+    traffic = measured_traffic(args.scheme, args.steps) if N == 2048 else None
     achieved = traffic / (avg_us * 1e-6) / 1e9 if traffic else None
     equivalent = bps32 / (avg_us * 1e-6) / 1e9
 

@@ -2,30 +2,31 @@
 // how deep and the launch; small boxes in LDS (lbm_tile.hip).
 #pragma once
 
-#include <mutex>
-
 #include "lbm_internal.h"
+#include "lds_limit.h"
 
 namespace lbm {
 
-// Kernels with more than 64 KB of dynamic LDS need their limit raised, on each
-// device they run on: once per device and kernel, under a lock.
-struct LdsLimit {
-    static constexpr int kMaxDevices = 64;
-    std::mutex m;
-    bool done[kMaxDevices] = {};
-    hipError_t raise(const void *fn, int bytes) {
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e != hipSuccess) return e;
-        if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-        std::lock_guard<std::mutex> lock(m);
-        if (done[dev]) return hipSuccess;
-        e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-        if (e == hipSuccess) done[dev] = true;
-        return e;
-    }
-};
+// value of the lane to the left (x - 1) or to the right (x + 1); 0 at the strip's edge
+template <int CTRL>
+__device__ __forceinline__ float lane_shift(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double v) {
+    typedef int int2_t __attribute__((ext_vector_type(2)));
+    int2_t w = __builtin_bit_cast(int2_t, v);
+    w.x = __builtin_amdgcn_update_dpp(0, w.x, CTRL, 0xf, 0xf, true);
+    w.y = __builtin_amdgcn_update_dpp(0, w.y, CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, w);
+}
+// The workgroup's place in an order that gives each of the 8 XCDs, over which the
+// hardware deals workgroups round robin, a contiguous run.
+__device__ __forceinline__ int block_in_xcd_order() {
+    const int nb = gridDim.x, per = (nb + 7) >> 3, full = nb & 7;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    return full == 0 || xcd <= full ? xcd * per + slot : full * per + (xcd - full) * (per - 1) + slot;
+}
 
 // One lattice as a buffer: a slot at a wave-uniform byte offset plus a lane's.  The
 // hardware drops a store whose lane offset lies past the buffer, so a lane that has

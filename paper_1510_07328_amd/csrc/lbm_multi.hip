@@ -45,19 +45,6 @@ using Lat = D2Q9;
 constexpr int Q = Lat::Q;
 constexpr int kWaves = 4;  // wavefronts per workgroup, neighbouring strips of one segment
 
-// value of the lane to the left (x - 1) or to the right (x + 1); 0 at the strip's edge
-template <int CTRL>
-__device__ __forceinline__ float lane_shift(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double lane_shift(double v) {
-    typedef int int2_t __attribute__((ext_vector_type(2)));
-    int2_t w = __builtin_bit_cast(int2_t, v);
-    w.x = __builtin_amdgcn_update_dpp(0, w.x, CTRL, 0xf, 0xf, true);
-    w.y = __builtin_amdgcn_update_dpp(0, w.y, CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, w);
-}
 // the population q of the cell x, from the lane of x - e_qx
 template <int EX, typename T>
 __device__ __forceinline__ T from_x(T v) {
@@ -154,11 +141,8 @@ __global__ void __launch_bounds__(64 * kWaves, (MODE ? 1 : sizeof(T) == 8 ? 2 : 
             Force<T> F, int strips, int ly, int nwaves) {
     constexpr int WO = 64 - 2 * (H - 1);  // columns a strip writes
     constexpr uint32_t XM = link_bits(0, -1), XP = link_bits(0, 1), YM = link_bits(1, -1), YP = link_bits(1, 1);
-    // neighbouring strips and segments share the lines at their edges: give each
-    // XCD (workgroups go round robin over the 8) a contiguous run of them
-    const int nb = gridDim.x, per = (nb + 7) >> 3, full = nb & 7;
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int blk = full == 0 || xcd <= full ? xcd * per + slot : full * per + (xcd - full) * (per - 1) + slot;
+    // neighbouring strips and segments share the lines at their edges
+    const int blk = block_in_xcd_order();
     const int wid = __builtin_amdgcn_readfirstlane(blk * kWaves + (int)(threadIdx.x >> 6));
     if (wid >= nwaves) return;
     const int strip = wid % strips, seg = wid / strips;

@@ -41,18 +41,6 @@ namespace {
 using Lat = D3Q19;
 constexpr int Q = Lat::Q;
 
-template <int CTRL>
-__device__ __forceinline__ float lane_shift(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double lane_shift(double v) {
-    typedef int int2_t __attribute__((ext_vector_type(2)));
-    int2_t w = __builtin_bit_cast(int2_t, v);
-    w.x = __builtin_amdgcn_update_dpp(0, w.x, CTRL, 0xf, 0xf, true);
-    w.y = __builtin_amdgcn_update_dpp(0, w.y, CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, w);
-}
 // value of the lane at x - ex (ex a compile-time constant after unrolling)
 template <typename T>
 __device__ __forceinline__ T from_x(T v, int ex) {
@@ -85,10 +73,8 @@ __global__ void __launch_bounds__((64 * Rows3<T, KIND>::W)) k_multi3(const T *__
     constexpr int W = Rows3<T, KIND>::W, R = Rows3<T, KIND>::R, NW = W * R;
     extern __shared__ unsigned char smem3[];
     T(*lds)[NYQ][W][64] = reinterpret_cast<T(*)[NYQ][W][64]>(smem3);
-    // neighbouring windows share lines: a contiguous run of them per XCD
-    const int nb = gridDim.x, per = (nb + 7) >> 3, full = nb & 7;
-    const int xcd = blockIdx.x & 7, place = blockIdx.x >> 3;
-    const int blk = full == 0 || xcd <= full ? xcd * per + place : full * per + (xcd - full) * (per - 1) + place;
+    // neighbouring windows share lines
+    const int blk = block_in_xcd_order();
     const int strip = blk % strips, group = (blk / strips) % groups, seg = blk / (strips * groups);
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int nx = b.nx, ny = b.ny, nz = b.nz;

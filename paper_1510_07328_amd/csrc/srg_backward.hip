@@ -24,7 +24,6 @@ namespace {
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int TB = 128;  // positions per tile
 
@@ -66,7 +65,8 @@ struct Split3 {
     }
 };
 
-// GELU(z) and GELU'(z) of one value, sharing the error function
+// GELU(z) and GELU'(z) = Phi(z) + z phi(z), phi(z) = exp(-z^2 / 2) / sqrt(2 pi), of one
+// value, sharing the error function's exponential
 __device__ __forceinline__ void gelu_both(float z, float &g, float &dg) {
     const ErfExp q = erf_exp(z * 0.70710678118654752f);
     g = 0.5f * z * (1.0f + q.erf);

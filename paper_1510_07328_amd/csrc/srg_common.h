@@ -8,6 +8,8 @@
 #include <mutex>
 #include <type_traits>
 
+#include "lds_limit.h"
+
 namespace srg {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
@@ -41,11 +43,6 @@ __device__ __forceinline__ ErfExp erf_exp(float x) {
 // GELU(z) = z Phi(z) = z (1 + erf(z / sqrt 2)) / 2
 __device__ __forceinline__ float gelu(float z) {
     return 0.5f * z * (1.0f + erf_exp(z * 0.70710678118654752f).erf);
-}
-// GELU'(z) = Phi(z) + z phi(z), phi(z) = exp(-z^2 / 2) / sqrt(2 pi)
-__device__ __forceinline__ float gelu_grad(float z) {
-    const ErfExp q = erf_exp(z * 0.70710678118654752f);
-    return __builtin_fmaf(z * 0.39894228040143268f, q.e, 0.5f * (1.0f + q.erf));
 }
 __device__ __forceinline__ __bf16 to_bf(float v) { return (__bf16)v; }
 __device__ __forceinline__ float to_f(__bf16 v) { return (float)v; }
@@ -164,24 +161,8 @@ __device__ __forceinline__ float feature(const float *__restrict__ nu, const flo
 
 constexpr int RS = CH + 8;  // LDS row stride of a 64-channel activation row, in elements (144 bytes)
 
-// Kernels with more than 64 KB of dynamic LDS need their limit raised, on each
-// device they run on: once per device and kernel, under a lock.
-constexpr int kMaxDevices = 64;
-struct LdsLimit {
-    std::mutex m;
-    bool done[kMaxDevices] = {};
-    hipError_t raise(const void *fn, int bytes) {
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e != hipSuccess) return e;
-        if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-        std::lock_guard<std::mutex> lock(m);
-        if (done[dev]) return hipSuccess;
-        e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-        if (e == hipSuccess) done[dev] = true;
-        return e;
-    }
-};
+using lbm::kMaxDevices;
+using lbm::LdsLimit;
 
 // Compute units of the current device (cached per device).
 inline int device_cus() {

@@ -41,7 +41,7 @@ METRIC = "MLUPS & % HBM roofline (FP32-dev vs FP64) at ≤1e-6 rel err; surrogat
 # WRITE_SIZE runs (read counter scaled by 2.0, write by 1.0, the factors a 1 GiB device copy
 # reads), valid for the kernel and layout sources whose combined sha256 prefix is the key.
 # profiles/k_multi_d2v9.md holds the counts.
-MEASURED_TRAFFIC = {"a89cf7e8299b5e37": {"aa": {20: 70_620_000, 200: 62_620_000}, "push": {20: 70_580_000, 200: 62_610_000}}}
+MEASURED_TRAFFIC = {"788bfdff14b9b2fe": {"aa": {20: 70_620_000, 200: 62_620_000}, "push": {20: 70_580_000, 200: 62_610_000}}}
 _CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_1510_07328_amd", "csrc")
 KERNEL_SRCS = [os.path.join(_CSRC, f) for f in ("lbm_kernels.hip", "lbm_collide.h", "lbm_internal.h",
                                                   "lbm_capi.hip", "lbm_multi.hip", "lbm_multi.h")]

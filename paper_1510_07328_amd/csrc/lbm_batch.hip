@@ -48,11 +48,11 @@ using Lat = D2Q9;
 // step into its own slot -q.  Every cell so reads and writes by one rule, at a
 // lane's column plus compile-time offsets (the planes and rows are the LDS
 // instructions' immediate offsets), and only a wavefront that holds an edge does
-// the extra writes: about 103 vector instructions per update, of which 99 are the
-// collision (123 before, with the slot addresses formed in every step and the two
+// the extra writes: 102 vector instructions per cell of the window and step by counters,
+// of which 99 are the collision, or 117 per update that is kept (halo columns are 64 of
+// 512; 123 per cell before, with the slot addresses formed in every step and the two
 // edge wavefronts of a row selecting them per lane).  512 tubes of 256 to 8192
-// columns, 4 nx steps each: 273 -> 214 ms, 350 GLUPS: vector issue with the halo
-// columns (512 of 448) counted.
+// columns, 4 nx steps each: 273 -> 214 ms, 350 GLUPS, bound by vector issue.
 // Cell k of a thread is k BLOCK + threadIdx.x of the 4 x WP grid (row = cell / WP).
 template <int WP, int BLOCK, typename T, bool O3>
 __global__ void __launch_bounds__(BLOCK) k_batch_round(T *__restrict__ buf0, T *__restrict__ buf1,

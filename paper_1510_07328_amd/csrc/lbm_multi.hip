@@ -325,6 +325,12 @@ int multi_depth(const MultiPlan &p, int64_t n, int odd) {
 // pipelines (their wavefronts run a few rows each), large ones deep (the traffic
 // is divided by H, the issue of about 102 vector instructions per update is
 // not: at 4096^2 and H = 6 it takes 55 of the 63 us).
+// The rule takes 4 wavefronts per SIMD in float32 and 2 in float64; fewer fit the deep
+// pipelines (float32 H = 6: 3, with links 2; float64 with walls H = 6 and with solids H = 4
+// and 6: 1).  With links at the rule's choice and at the best depth and segment (one AA step
+// per kernel): walls 1000^2 6.3, 6.3 (13.7), 2048^2 21.0, 19.4 (47.6), 4096^2 74, 70 (261),
+// float64 8.8, 8.7 (24.5), 33.6, 31.9 (110), 122, 121 (486); solids 8.0, 7.8 (15.7), 26.6,
+// 23.6 (52), 90, 88 (282), float64 12.5, 10.5 (26.2), 44, 42 (117), 160, 157 (513).
 MultiPlan multi_plan(int nx, int ny, int fp64, bool links, bool single, int cus) {
     MultiPlan p{};
     const double row = fp64 ? 0.30 : links ? 0.25 : 0.20, bytes = 9.0 * (fp64 ? 8 : 4) * (double)nx * ny;

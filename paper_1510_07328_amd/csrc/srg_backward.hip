@@ -192,7 +192,8 @@ __global__ void __launch_bounds__(256) k_bwd_out(const float *__restrict__ dout,
 // FIRST: the layer below is layer 1, whose dz is needed only for its weights:
 // dzp stays in LDS and dW1[tap][co][c] = sum_y dzp[y, co] f[c, y + tap - 2],
 // db1 = sum dzp follow there, the 15 features of a position (in three bfloat16
-// terms) and a one for the bias as the 16 columns of v_mfma_f32_16x16x32_bf16.
+// terms) and a one for the bias as the 16 columns of v_mfma_f32_16x16x32_bf16.  That
+// variant takes all 256 registers and spills 9 more.
 // ---------------------------------------------------------------------------
 template <int D>
 struct BwdTile {

@@ -37,11 +37,13 @@ CORR = 32.0
 METRIC = "MLUPS & % HBM roofline (FP32-dev vs FP64) at ≤1e-6 rel err; surrogate speedup"
 
 # HBM bytes per step of the 2048^2 field in calls of 20 steps (passes of 4, 4, 6 and 6) and of
-# 200 (32 of 6 and 2 of 4; longer calls have fewer of 4 still), from rocprofv3 FETCH_SIZE and
+# 200 (32 of 6 and 2 of 4; longer calls have fewer of 4 still), aa_odd: after an odd number of AA
+# steps, where the first and the last step of a call run alone; from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE runs (read counter scaled by 2.0, write by 1.0, the factors a 1 GiB device copy
 # reads), valid for the kernel and layout sources whose combined sha256 prefix is the key.
 # profiles/k_multi_d2v9.md holds the counts.
-MEASURED_TRAFFIC = {"788bfdff14b9b2fe": {"aa": {20: 70_620_000, 200: 62_620_000}, "push": {20: 70_580_000, 200: 62_610_000}}}
+MEASURED_TRAFFIC = {"788bfdff14b9b2fe": {"aa": {20: 70_620_000, 200: 62_620_000}, "aa_odd": {20: 99_500_000, 200: 65_500_000},
+                                         "push": {20: 70_580_000, 200: 62_610_000}}}
 _CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_1510_07328_amd", "csrc")
 KERNEL_SRCS = [os.path.join(_CSRC, f) for f in ("lbm_kernels.hip", "lbm_collide.h", "lbm_internal.h",
                                                   "lbm_capi.hip", "lbm_multi.hip", "lbm_multi.h")]
@@ -59,9 +61,12 @@ def kernel_hash() -> str:
     return h.hexdigest()[:16]
 
 
-def measured_traffic(scheme: str, steps: int):
-    """Counter bytes per step of calls of `steps` steps, None where that call was not measured."""
-    return MEASURED_TRAFFIC.get(kernel_hash(), {}).get(scheme, {}).get(min(steps, 200))
+def measured_traffic(scheme: str, steps: int, warmup: int = 0):
+    """Counter bytes per step of calls of `steps` steps after `warmup`, None where that was not measured."""
+    if steps % 2:
+        return None
+    kind = "aa_odd" if scheme == "aa" and warmup % 2 else scheme
+    return MEASURED_TRAFFIC.get(kernel_hash(), {}).get(kind, {}).get(min(steps, 200))
 
 
 EXTRAS = ("order3", "out_of_cache", "batched", "d3v19", "surrogate", "porous", "weights", "order4")
@@ -570,7 +575,7 @@ def main():
     lat32.free()
     mlups32 = cells * args.steps / (ms32 * 1e-3) / 1e6
     avg_us = ms32 * 1e3 / args.steps
-    traffic = measured_traffic(args.scheme, args.steps) if N == 2048 else None
+    traffic = measured_traffic(args.scheme, args.steps, args.warmup) if N == 2048 else None
     achieved = traffic / (avg_us * 1e-6) / 1e9 if traffic else None
     equivalent = bps32 / (avg_us * 1e-6) / 1e9
 

@@ -26,4 +26,7 @@ def test_recorded_traffic_is_that_of_the_timed_call():
     for scheme in ("aa", "push"):
         short, long = bench.measured_traffic(scheme, 20), bench.measured_traffic(scheme, 200)
         assert short > 1.1 * long and bench.measured_traffic(scheme, 10000) == long
-        assert bench.measured_traffic(scheme, 30) is None
+        assert bench.measured_traffic(scheme, 30) is None and bench.measured_traffic(scheme, 201) is None
+    # after an odd warm-up an AA call starts and ends with a single step
+    assert bench.measured_traffic("aa", 20, 5) > 1.3 * bench.measured_traffic("aa", 20, 4)
+    assert bench.measured_traffic("push", 20, 5) == bench.measured_traffic("push", 20)
